@@ -151,7 +151,7 @@ static hipError_t launch_bwd_ue(const FieldPtrs<T>& p, int model, hipStream_t st
 
 // independent Gaussian: FP32 30x30 outputs (32x32 stencils, four per
 // thread), so the ring of halo stencils is 12% of the work against 24% for
-// 14x14; FP64 keeps 14x14 (one stencil per thread: its 250 registers leave
+// 14x14; FP64 keeps 14x14 (one stencil per thread: its 239 registers leave
 // no room for a second)
 template <typename T>
 static hipError_t launch_bwd_gauss(const FieldPtrs<T>& p, hipStream_t st) {

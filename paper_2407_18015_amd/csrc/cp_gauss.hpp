@@ -11,16 +11,37 @@
 // and neighbour n enters through z_n = (t - d_n) r_n with
 // d_n = (mu_n - mu_v) / sigma_v and r_n = sigma_v / sigma_n.
 // The sweep covers t in [-C, C] (the rest of phi weighs 2e-9 for C = 6 and
-// 1.3e-17 for C = 8.5) and cuts it at the points d_n + c_k / r_n of every
-// neighbour and c_k of the vertex, c_k running over K fixed multiples of the
-// standard deviation in [-C, C].  Every panel therefore spans at most
-// ~2 (FP32) or ~1.5 (FP64) standard deviations of every distribution that
-// varies on it, and a fixed Gauss-Legendre rule of N nodes integrates it to
-// ~1e-8 (FP32: C = 6, c = 0, +-2, +-4, +-6, N = 6) or ~1e-14 (FP64:
-// C = 8.5, c = 0, +-1.5, +-3, +-4.5, +-6, +-8.5, N = 10) absolute over the
-// whole integral.  S and F come from one erfc of |z|, so both tails keep full
-// relative precision.  The cuts are merged on the fly by one cursor per
-// distribution (each sequence is already sorted), as in the histogram sweep.
+// 1.3e-17 for C = 8.5).
+//
+// Nodes.  The integrand is an entire function that decays like a Gaussian, so
+// the trapezoidal rule converges exponentially: its error is the integrand's
+// Fourier transform at multiples of 2 pi / h, and the transform of a product
+// of phi and the four Phi((t - d_n) r_n) (or of phi, a density of one
+// neighbour and the other Phi) falls off like exp(-w^2 / (2 V)), V = 1 + sum
+// of r_n^2 over the neighbours that vary inside the window.  With
+// h = 2 pi / sqrt(2 Lam V) the error is about exp(-Lam): below 8e-9 for
+// Lam = 17 (FP32) and 1e-15 for Lam = 32 (FP64) over random stencils with
+// ratios up to e^2, probabilities and derivative integrands alike.  Five
+// equal sigmas take 27 nodes (FP64: 52); fitted fields of 20 members, whose
+// sigmas differ by up to a factor of two or three, about 30 to 45.
+// A neighbour much narrower than the vertex makes h small everywhere although
+// the integrand is steep only near d_n.  There the rule is composite
+// Gauss-Legendre instead: the window is cut at d_n + c_k / r_n of every
+// neighbour and at c_k of the vertex, c_k running over K fixed multiples of
+// the standard deviation in [-C, C] (FP32: 0, +-2, +-4, +-6, six nodes a
+// panel; FP64: 0, +-1.5, +-3, +-4.5, +-6, +-8.5, ten nodes), so that a panel
+// spans at most ~2 (1.5) deviations of every distribution that varies on it:
+// ~1e-8 (~1e-14) absolute for any ratio, with 150 to 200 nodes (400 to 550)
+// for overlapping supports.  Each vertex takes the rule with fewer nodes.
+// Both kinds run through one node loop, so a wave that holds both pays the
+// longer of the two, not their sum.
+//
+// Bound by vector issue (the tails: one reciprocal, one exponential and nine
+// fused multiply-adds each).  Measured at 1024^2 on a 20-member fit, FP32,
+// composite rule for every vertex -> this: classification 544 -> 92 us,
+// adjoint 1156 -> 161 us; at 512^2 in FP64 with sigmas within a factor of two
+// 2.16 -> 0.25 and 3.85 -> 0.44 ms.  Sigmas drawn over a factor of 300 (most
+// waves then hold composite vertices): 165 -> 164 and 564 -> 455 us at 512^2.
 #pragma once
 
 #include <cmath>
@@ -30,262 +51,286 @@
 
 namespace cp {
 
+// hc: step of the trapezoidal rule at V = 1, 2 pi / sqrt(2 Lam)
 template <typename T>
 struct GaussRule;
 template <>
 struct GaussRule<float> {
   static constexpr int K = 7, N = 6;
   static constexpr float c[7] = {-6.f, -4.f, -2.f, 0.f, 2.f, 4.f, 6.f};
+  static constexpr double hc = 1.07755;
+  static constexpr float scale = kTailScale;  // of a deviate in gauss_tail
 };
 template <>
 struct GaussRule<double> {
   static constexpr int K = 11, N = 10;
   static constexpr double c[11] = {-8.5, -6.0, -4.5, -3.0, -1.5, 0.0, 1.5, 3.0, 4.5, 6.0, 8.5};
+  static constexpr double hc = 0.78539816339744830962;
+  static constexpr double scale = 0.70710678118654752440;
 };
 
-// erfc(x) for x >= 0 and e^x for x <= 0 (the only arguments here).  FP32 on
-// the device: the hardware-instruction forms of cp_mc_math.hpp (fractional
-// error below ~2e-7, against ~1e-7 for the library functions); FP64 and
-// host code: the C library.
-CP_HD float gerfc(float x) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return erfc_pos(x);
-#else
-  return erfcf(x);
-#endif
+// Normal density factor and upper tail of |z| from the scaled deviate
+// zs = z GaussRule::scale: e = exp(-z^2 / 2), q = Pr(N(0,1) > |z|).  FP32 in the
+// hardware-instruction form of cp_mc_math.hpp (the exponential is shared);
+// FP64: the C library.
+CP_HD void gauss_tail(float zs, float& q, float& e) { upper_tail(zs, q, e); }
+CP_HD void gauss_tail(double zs, double& q, double& e) {
+  q = 0.5 * erfc(fabs(zs));
+  e = exp(-zs * zs);
 }
-CP_HD double gerfc(double x) { return erfc(x); }
-CP_HD float gexp(float x) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return exp_neg(x);
-#else
-  return expf(x);
-#endif
-}
-CP_HD double gexp(double x) { return exp(x); }
+CP_HD float gauss_density(float zs) { return exp2_neg(-zs * zs); }
+CP_HD double gauss_density(double zs) { return exp(-zs * zs); }
 
-// out = (P_min, P_max, t1, t2) of a vertex with valid parameters; neighbour
-// order e, n, w, s; absent neighbours contribute 1; the saddle terms are
-// computed only when `interior` (all four present) and are 0 otherwise.
-template <typename T>
-CP_HD void gauss_vertex(T mv, T sv, const T (&mn)[4], const T (&sn)[4], const bool (&pres)[4], T (&out)[4]) {
+// A stencil in vertex units and its rule; P: the type of z_n = (t - d) rs
+// (rs = r times the rule's scale).  An absent neighbour has rs = 0, so it sits at its
+// median (S = F = 1/2) everywhere and the caller multiplies by 2 for each; its
+// d lies outside every window and s = 0 gives it no cuts.
+template <typename T, typename P>
+struct GaussPlan {
+  P d[4], rs[4];
+  T s[4];
+  T h;          // step of the trapezoidal rule, nodes i h, |i| <= m
+  int m;
+  bool panels;  // composite rule instead
+  // cut ck of neighbour n (any nearby point serves as well: held in T)
+  CP_HD T cut(int n, T ck) const { return cfma(ck, s[n], T(d[n])); }
+  // x in deviations of neighbour n
+  CP_HD T dev(int n, T x) const { return (x - T(d[n])) * T(rs[n]) * (T(1) / GaussRule<T>::scale); }
+
+  // The smallest cut of neighbour n above x0, C if there is none.  FP32: the
+  // cuts lie two deviations apart, so it is found from x0's own deviation, to
+  // within one by rounding.
+  CP_HD T next_cut(int n, T x0) const {
+    using R = GaussRule<T>;
+    constexpr T C = R::c[R::K - 1];
+    T c = C;
+    if constexpr (sizeof(T) == 4) {
+      const T k = T(2) * floor(T(0.5) * dev(n, x0)) + T(2);
+      const T k1 = tmax(k, -C), c1 = cut(n, k1), k2 = k1 + T(2), c2 = cut(n, k2);
+      c = k2 <= C && c2 > x0 ? c2 : c;
+      c = k1 <= C && c1 > x0 ? c1 : c;
+    } else {
+#pragma unroll
+      for (int j = R::K - 1; j >= 0; --j) {
+        const T v = cut(n, R::c[j]);
+        c = v > x0 ? v : c;
+      }
+    }
+    return c;
+  }
+  // cuts of neighbour n inside the window (FP32: to within one by rounding)
+  CP_HD T cuts_inside(int n) const {
+    using R = GaussRule<T>;
+    constexpr T C = R::c[R::K - 1];
+    T v = T(0);
+    if constexpr (sizeof(T) == 4) {
+      const T hi = floor(T(0.5) * tmin(dev(n, C), C)), lo = ceil(T(0.5) * tmax(dev(n, -C), -C));
+      v = tmax(hi - lo + T(1), T(0));
+    } else {
+#pragma unroll
+      for (int j = 0; j < R::K; ++j) v += cut(n, R::c[j]) > -C && cut(n, R::c[j]) < C ? T(1) : T(0);
+    }
+    return v;
+  }
+};
+
+// FP32 steps keep 12 significant bits, so the nodes i h are exact
+CP_HD float gauss_round_step(float h) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, h) & 0xfffff000u);
+}
+CP_HD double gauss_round_step(double h) { return h; }
+
+template <typename T, typename P>
+CP_HD void gauss_plan(GaussPlan<T, P>& g, T mv, T sv, const T (&mn)[4], const T (&sn)[4], const bool (&pres)[4]) {
   using R = GaussRule<T>;
   constexpr int K = R::K, N = R::N;
   constexpr T C = R::c[K - 1];
-  const T big = T(4) * C;  // beyond every panel end
-  const T isv = crcp(sv);
-  T d[4], s[4], r[4], nx[4];
-  int k[4];
+  const P isv = P(1) / P(sv);
+  T V = T(1);
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
-    d[n] = (mn[n] - mv) * isv;
-    s[n] = sn[n] * isv;
-    r[n] = sv * crcp(sn[n]);
-    k[n] = 0;
-    nx[n] = pres[n] ? cfma(T(R::c[0]), s[n], d[n]) : big;
-    // skip the cuts at or below the window start
-    for (int q = 0; q < K && pres[n] && !(nx[n] > -C); ++q) {
-      k[n] += 1;
-      nx[n] = k[n] < K ? cfma(T(R::c[k[n]]), s[n], d[n]) : big;
-    }
+    const P r = pres[n] ? P(sv) / P(sn[n]) : P(0);
+    g.d[n] = pres[n] ? (P(mn[n]) - P(mv)) * isv : P(4) * P(C);
+    g.s[n] = pres[n] ? T(P(sn[n]) * isv) : T(0);
+    g.rs[n] = r * P(GaussRule<T>::scale);
+    // constant on the window: no bandwidth
+    if (g.cut(n, -C) < C && g.cut(n, C) > -C) V = cfma(T(r), T(r), V);
   }
-  int kv = 1;
-  T nv = T(R::c[1]);
-  T x0 = -C;
-  T acc[4] = {T(0), T(0), T(0), T(0)};
-  constexpr T rs2 = T(0.70710678118654752440);
-  for (int it = 0; it < 5 * K; ++it) {
-    if (!(x0 < C)) break;
-    T x1 = nv;
+  g.h = gauss_round_step(T(R::hc) / sqrt(V));
+  // nodes of both rules, the composite one's counted only where it can win
+  const T nodes = T(2) * C / g.h + T(1);
+  g.panels = false;
+  if (nodes > T(N * (K - 1))) {
+    T cuts = T(K - 1);
 #pragma unroll
-    for (int n = 0; n < 4; ++n) x1 = tmin(x1, nx[n]);
-    const T mid = (x0 + x1) * T(0.5), hl = (x1 - x0) * T(0.5);
-    T p[4] = {T(0), T(0), T(0), T(0)};
+    for (int n = 0; n < 4; ++n) cuts += g.cuts_inside(n);
+    g.panels = !(nodes <= T(N) * cuts);
+  }
+  g.m = g.panels ? 0 : (int)(C / g.h);
+}
+
+// Visit the nodes of the plan in order: node(position in P, position, weight)
+// for each, flush() after at most N of them and at the end.
+template <typename T, typename P, typename Node, typename Flush>
+CP_HD void gauss_nodes(const GaussPlan<T, P>& g, Node node, Flush flush) {
+  using R = GaussRule<T>;
+  constexpr int K = R::K, N = R::N;
+  constexpr T C = R::c[K - 1];
+  T x0 = -C, x1 = C;
+  int i = -g.m;
+  for (;;) {
+    if (g.panels) {
+      // the next cut after x0 (strictly: every panel makes progress)
+      x1 = C;
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const T t = cfma(hl, T(GL<N>::x[j]), mid);
-      const T phi = T(GL<N>::w[j]) * gexp(T(-0.5) * t * t);
-      T q0 = phi, q1 = phi, q2 = phi, q3 = phi;
+      for (int k = 1; k < K - 1; ++k) x1 = T(R::c[k]) > x0 && T(R::c[k]) < x1 ? T(R::c[k]) : x1;
 #pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        if (!pres[n]) continue;
-        const T z = (t - d[n]) * r[n];
-        const T e = T(0.5) * gerfc(fabs(z) * rs2);
-        const T S = z > T(0) ? e : T(1) - e;
-        const T F = z > T(0) ? T(1) - e : e;
-        q0 *= S;
-        q1 *= F;
-        // e, w (n = 0, 2) take S in t1 and F in t2; n, s the reverse
-        q2 *= (n & 1) ? F : S;
-        q3 *= (n & 1) ? S : F;
-      }
-      p[0] += q0;
-      p[1] += q1;
-      p[2] += q2;
-      p[3] += q3;
+      for (int n = 0; n < 4; ++n) x1 = tmin(x1, g.next_cut(n, x0));
     }
+    // two nodes at a time: independent work to issue while one waits on its
+    // transcendentals.  No more than that: it would cost occupancy.
+#pragma unroll 1
+    for (int j = 0; j < N; j += 2) {
+      if (!g.panels && i > g.m) break;
+      P tp[2];
+      T t[2], w[2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] = cfma(p[q], hl, acc[q]);
-    // advance every cursor that sits at x1
-    if (nv == x1) {
-      kv += 1;
-      nv = kv < K ? T(R::c[kv]) : big;
-    }
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-      if (nx[n] == x1) {
-        k[n] += 1;
-        nx[n] = k[n] < K ? cfma(T(R::c[k[n]]), s[n], d[n]) : big;
+      for (int u = 0; u < 2; ++u) {
+        if (g.panels) {
+          const P hl = (P(x1) - P(x0)) * P(0.5);
+          tp[u] = cfma(hl, P(GL<N>::x[j + u]), (P(x0) + P(x1)) * P(0.5));
+          t[u] = T(tp[u]);
+          w[u] = T(hl) * T(GL<N>::w[j + u]);
+        } else {
+          t[u] = T(i + u) * g.h;
+          tp[u] = P(t[u]);
+          w[u] = i + u > g.m ? T(0) : g.h;
+        }
       }
+      i += 2;
+      node(tp[0], t[0], w[0]);
+      node(tp[1], t[1], w[1]);
+    }
+    flush();
     x0 = x1;
+    if (g.panels ? !(x1 < C) : i > g.m) break;
   }
-  constexpr T inv_sqrt_2pi = T(0.39894228040143267794);
+}
+
+// out = (P_min, P_max, t1, t2) of a vertex with valid parameters; neighbour
+// order e, n, w, s; absent neighbours contribute 1; the saddle terms are 0
+// unless all four are present.
+template <typename T>
+CP_HD void gauss_vertex(T mv, T sv, const T (&mn)[4], const T (&sn)[4], const bool (&pres)[4], T (&out)[4]) {
+  GaussPlan<T, T> g;
+  gauss_plan(g, mv, sv, mn, sn, pres);
+  T acc[4] = {T(0), T(0), T(0), T(0)};
+  const auto node = [&](T, T t, T w) {
+    T S[4], F[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const T z = (t - g.d[n]) * g.rs[n];
+      T q, e;
+      gauss_tail(z, q, e);
+      S[n] = z > T(0) ? q : T(1) - q;
+      F[n] = z > T(0) ? T(1) - q : q;
+    }
+    // e, w (n = 0, 2) take S in t1 and F in t2; n, s the reverse
+    const T phi = w * gauss_density(t * GaussRule<T>::scale);
+    const T sa = phi * (S[0] * S[2]), fa = phi * (F[0] * F[2]), sb = S[1] * S[3], fb = F[1] * F[3];
+    acc[0] = cfma(sa, sb, acc[0]);
+    acc[1] = cfma(fa, fb, acc[1]);
+    acc[2] = cfma(sa, fb, acc[2]);
+    acc[3] = cfma(fa, sb, acc[3]);
+  };
+  gauss_nodes(g, node, [] {});
+  T scale = T(0.39894228040143267794);  // 1 / sqrt(2 pi)
+#pragma unroll
+  for (int n = 0; n < 4; ++n) scale *= pres[n] ? T(1) : T(2);
   const bool interior = pres[0] && pres[1] && pres[2] && pres[3];
-  out[0] = acc[0] * inv_sqrt_2pi;
-  out[1] = acc[1] * inv_sqrt_2pi;
-  out[2] = interior ? acc[2] * inv_sqrt_2pi : T(0);
-  out[3] = interior ? acc[3] * inv_sqrt_2pi : T(0);
+  out[0] = acc[0] * scale;
+  out[1] = acc[1] * scale;
+  out[2] = interior ? acc[2] * scale : T(0);
+  out[3] = interior ? acc[3] * scale : T(0);
 }
 
 // Weighted Jacobian of one stencil: jac[2 slot + q] = g_min dP_min/dtheta_q
 // + g_max dP_max/dtheta_q, theta = (mu, sigma), slots v, e, n, w, s (absent
-// neighbours: 0); also P_min and P_max.  In vertex units, with
-// p_n(x) = phi(z_n) / sigma_n the density of neighbour n:
+// neighbours: 0).  In vertex units, with p_n(x) = phi(z_n) / sigma_n the
+// density of neighbour n:
 //   dP_min/dmu_n    = int phi(t) p_n prod_{k!=n} S_k dt,
 //   dP_min/dsigma_n = int phi(t) p_n z_n prod_{k!=n} S_k dt,
 // and for P_max the same with F and the opposite sign (dF = -dS).  The
 // vertex slot follows from translation invariance (dP/dmu_v = -sum_n
 // dP/dmu_n) and scale invariance about mu_v (sigma_v dP/dsigma_v = -sum_n
-// ((mu_n - mu_v) dP/dmu_n + sigma_n dP/dsigma_n)).  Same panels and rule as
-// gauss_vertex; the leave-one-out products come from prefix / suffix
-// products.
+// ((mu_n - mu_v) dP/dmu_n + sigma_n dP/dsigma_n)).  Same nodes as
+// gauss_vertex; the density of a neighbour is the exponential its tail uses.
+//
+// Positions (nodes, z_n) in FP64 for both dtypes: in FP32 a panel node's t
+// carries half an ulp of |t| <= 6 (2.4e-7), which z_n multiplies by
+// sigma_v / sigma_n; the derivative integrands p_n z_n would inherit a
+// relative error of that size for narrow neighbours.  The factors (tails,
+// densities) and the sums over up to N nodes stay in T, the sums of those in
+// FP64: dP/dsigma_n cancels between the nodes below and above the
+// neighbour's mean.  The upstream weights enter at every node (g_min times
+// the S integrand, -g_max times the F one, one sum per derivative).
 template <typename T>
 CP_HD void gauss_vertex_jac(T mv, T sv, const T (&mn)[4], const T (&sn)[4], const bool (&pres)[4], T gmin,
-                            T gmax, T (&jac)[10], T& pmin, T& pmax) {
-  using R = GaussRule<T>;
-  // Positions (panel ends, nodes, z_n) in FP64 for both dtypes: in FP32 a
-  // node's t carries half an ulp of |t| <= 6 (2.4e-7), which z_n multiplies
-  // by sigma_v / sigma_n; the derivative integrands p_n z_n would inherit a
-  // relative error of that size for narrow neighbours.  The factors
-  // themselves (erfc, exp) and the sums stay in T.
+                            T gmax, T (&jac)[10]) {
   using P = double;
-  constexpr int K = R::K, N = R::N;
-  constexpr P C = R::c[K - 1];
-  const P big = P(4) * C;
-  const P isv = P(1) / P(sv);
-  P d[4], s[4], r[4], nx[4];
-  int k[4];
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    d[n] = (P(mn[n]) - P(mv)) * isv;
-    s[n] = P(sn[n]) * isv;
-    r[n] = P(sv) / P(sn[n]);
-    k[n] = 0;
-    nx[n] = pres[n] ? cfma(P(R::c[0]), s[n], d[n]) : big;
-    for (int q = 0; q < K && pres[n] && !(nx[n] > -C); ++q) {
-      k[n] += 1;
-      nx[n] = k[n] < K ? cfma(P(R::c[k[n]]), s[n], d[n]) : big;
-    }
-  }
-  int kv = 1;
-  P nv = P(R::c[1]);
-  P x0 = -C;
-  // panel sums in T (z_n keeps its sign on a panel: its mean is a cut), the
-  // sums over panels in FP64: dP/dsigma_n cancels between the panels below
-  // and above the neighbour's mean.  The upstream weights enter at every
-  // node (g_min times the S integrand, -g_max times the F one, one sum per
-  // derivative): half the accumulators of separate P_min and P_max sums.
-  P fS = P(0), fF = P(0);
+  GaussPlan<T, P> g;
+  gauss_plan(g, mv, sv, mn, sn, pres);
   P a[4] = {P(0), P(0), P(0), P(0)}, b[4] = {P(0), P(0), P(0), P(0)};
+  T qa[4] = {T(0), T(0), T(0), T(0)}, qb[4] = {T(0), T(0), T(0), T(0)};
   const T ngmax = -gmax;
-  constexpr T rs2 = T(0.70710678118654752440);
-  for (int it = 0; it < 5 * K; ++it) {
-    if (!(x0 < C)) break;
-    P x1 = nv;
-#pragma unroll
-    for (int n = 0; n < 4; ++n) x1 = tmin(x1, nx[n]);
-    const P mid = (x0 + x1) * P(0.5), hlp = (x1 - x0) * P(0.5);
-    const T hl = T(hlp);
-    T pS = T(0), pF = T(0), qa[4], qb[4];
-#pragma unroll
-    for (int n = 0; n < 4; ++n) qa[n] = qb[n] = T(0);
-    // the node loop stays a loop (the rule's nodes and weights are read from
-    // constant memory): unrolled, its live values do not fit the registers
-#pragma unroll 1
-    for (int j = 0; j < N; ++j) {
-      const P tp = cfma(hlp, P(GL<N>::x[j]), mid);
-      const T t = T(tp);
-      const T phi = T(GL<N>::w[j]) * gexp(T(-0.5) * t * t);
-      T S[4], F[4], z[4], pz[4];
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        S[n] = F[n] = T(1);
-        z[n] = pz[n] = T(0);
-        if (!pres[n]) continue;
-        z[n] = T((tp - d[n]) * r[n]);
-        const T e = T(0.5) * gerfc(fabs(z[n]) * rs2);
-        S[n] = z[n] > T(0) ? e : T(1) - e;
-        F[n] = z[n] > T(0) ? T(1) - e : e;
-        pz[n] = gexp(T(-0.5) * z[n] * z[n]);
-      }
-      // prefix products carry the node weight and the vertex density
-      T preS[5], preF[5], sufS[5], sufF[5];
-      preS[0] = preF[0] = phi;
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        preS[n + 1] = preS[n] * S[n];
-        preF[n + 1] = preF[n] * F[n];
-      }
-      sufS[4] = sufF[4] = T(1);
-#pragma unroll
-      for (int n = 3; n >= 0; --n) {
-        sufS[n] = sufS[n + 1] * S[n];
-        sufF[n] = sufF[n + 1] * F[n];
-      }
-      pS += preS[4];
-      pF += preF[4];
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        const T l = pz[n] * cfma(gmin, preS[n] * sufS[n + 1], ngmax * (preF[n] * sufF[n + 1]));
-        qa[n] += l;
-        qb[n] = cfma(l, z[n], qb[n]);
-      }
-    }
-    fS = cfma(P(pS), hlp, fS);
-    fF = cfma(P(pF), hlp, fF);
+  const auto node = [&](P tp, T t, T w) {
+    const T phi = w * gauss_density(t * GaussRule<T>::scale);
+    T S[4], F[4], z[4], e[4];
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      a[n] = cfma(P(qa[n]), hlp, a[n]);
-      b[n] = cfma(P(qb[n]), hlp, b[n]);
+      z[n] = T((tp - g.d[n]) * g.rs[n]);
+      T q;
+      gauss_tail(z[n], q, e[n]);
+      S[n] = z[n] > T(0) ? q : T(1) - q;
+      F[n] = z[n] > T(0) ? T(1) - q : q;
     }
-    if (nv == x1) {
-      kv += 1;
-      nv = kv < K ? P(R::c[kv]) : big;
-    }
+    // the pair products carry the node weight, the vertex density and the
+    // upstream weight
+    const T pS = phi * gmin, pF = phi * ngmax;
+    const T s01 = pS * (S[0] * S[1]), s23 = pS * (S[2] * S[3]), f01 = pF * (F[0] * F[1]), f23 = pF * (F[2] * F[3]);
+    const T l[4] = {cfma(S[1], s23, F[1] * f23), cfma(S[0], s23, F[0] * f23), cfma(S[3], s01, F[3] * f01),
+                    cfma(S[2], s01, F[2] * f01)};
 #pragma unroll
-    for (int n = 0; n < 4; ++n)
-      if (nx[n] == x1) {
-        k[n] += 1;
-        nx[n] = k[n] < K ? cfma(P(R::c[k[n]]), s[n], d[n]) : big;
-      }
-    x0 = x1;
-  }
-  constexpr T inv_sqrt_2pi = T(0.39894228040143267794), inv_2pi = T(0.15915494309189533577);
-  pmin = T(fS * P(inv_sqrt_2pi));
-  pmax = T(fF * P(inv_sqrt_2pi));
+    for (int n = 0; n < 4; ++n) {
+      const T v = e[n] * l[n];
+      qa[n] += v;
+      qb[n] = cfma(v, z[n], qb[n]);
+    }
+  };
+  const auto flush = [&] {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      a[n] += P(qa[n]);
+      b[n] += P(qb[n]);
+      qa[n] = qb[n] = T(0);
+    }
+  };
+  gauss_nodes(g, node, flush);
   // the vertex slot sums terms that cancel (the invariances): in FP64
-  P smu = P(0), ssg = P(0);
+  P smu = P(0), ssg = P(0), scale = P(0.15915494309189533577);  // 1 / (2 pi)
+#pragma unroll
+  for (int n = 0; n < 4; ++n) scale *= pres[n] ? P(1) : P(2);
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
     jac[2 + 2 * n] = jac[3 + 2 * n] = T(0);
     if (!pres[n]) continue;
-    const P c = P(inv_2pi) / P(sn[n]);
+    const P c = scale / P(sn[n]);
     const P dmu = c * a[n];  // g-weighted dP/dmu_n
-    const P dsg = c * b[n];  // g-weighted dP/dsigma_n
+    const P dsg = c / P(GaussRule<T>::scale) * b[n];  // g-weighted dP/dsigma_n
     jac[2 + 2 * n] = T(dmu);
     jac[3 + 2 * n] = T(dsg);
     smu += dmu;
-    ssg = cfma(d[n], dmu, cfma(s[n], dsg, ssg));
+    ssg = cfma(g.d[n], dmu, cfma(P(sn[n]) / P(sv), dsg, ssg));
   }
   jac[0] = T(-smu);
   jac[1] = T(-ssg);

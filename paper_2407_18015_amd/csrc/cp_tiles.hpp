@@ -127,7 +127,9 @@ CP_HD void vertex_jac_vals(T p0, T p1, const T (&q0)[4], const T (&q1)[4], const
     return;
   }
   if constexpr (MODEL == CP_GAUSSIAN) {
-    gauss_vertex_jac<T>(p0, p1, q0, q1, pres, gmin, gmax, jac, pmin, pmax);
+    static_assert(!WF, "the Gaussian adjoint does not evaluate the probabilities");
+    gauss_vertex_jac<T>(p0, p1, q0, q1, pres, gmin, gmax, jac);
+    pmin = pmax = T(0);
   } else if constexpr (MODEL == CP_UNIFORM) {
     const T Lv = p1 - p0, iLv = crcp(Lv);
     T a[4], b[4], iL[4];
@@ -366,10 +368,14 @@ __device__ __forceinline__ void tile_bwd_ue_impl(const FieldPtrs<T>& f, int ty0,
 
 template <typename T, int MODEL, int OX, int OY, int NT>
 __device__ __forceinline__ void tile_bwd_ue(const FieldPtrs<T>& f, int ty0, int tx0, T* lds, int tid) {
-  if (f.pmin)
-    tile_bwd_ue_impl<T, MODEL, OX, OY, NT, true>(f, ty0, tx0, lds, tid);
-  else
-    tile_bwd_ue_impl<T, MODEL, OX, OY, NT, false>(f, ty0, tx0, lds, tid);
+  // (the batched forward + adjoint takes no Gaussian fields)
+  if constexpr (MODEL != CP_GAUSSIAN) {
+    if (f.pmin) {
+      tile_bwd_ue_impl<T, MODEL, OX, OY, NT, true>(f, ty0, tx0, lds, tid);
+      return;
+    }
+  }
+  tile_bwd_ue_impl<T, MODEL, OX, OY, NT, false>(f, ty0, tx0, lds, tid);
 }
 
 template <int OX, int OY>
