@@ -13,6 +13,13 @@ namespace cp {
 constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
 constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
 
+// a ^ b ^ c in one instruction (the compiler makes two v_xor_b32 of it, twenty
+// of the hundred-odd instructions of a block): Gaussian Monte Carlo forward at
+// 500^2 x 2000 samples 1.90 -> 1.70 ms, adjoint at 512^2 x 1000 1.12 -> 1.04.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // Ten rounds on the counter c in place, key (k0, k1).  Each round's two
 // 32 x 32 -> 64-bit products are formed whole (one v_mad_u64_u32 each rather
 // than a high and a low multiply: a third faster on gfx950).
@@ -20,7 +27,11 @@ __device__ __forceinline__ void philox(uint32_t c[4], uint32_t k0, uint32_t k1) 
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)kPhiloxM0 * c[0], p1 = (uint64_t)kPhiloxM1 * c[2];
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
+    // (the first two rounds' words are mostly wave-uniform in the samplers:
+    // left to the scalar unit)
+    const uint32_t h1 = (uint32_t)(p1 >> 32), h0 = (uint32_t)(p0 >> 32);
+    const uint32_t n0 = r < 2 ? h1 ^ c[1] ^ k0 : xor3(h1, c[1], k0);
+    const uint32_t n2 = r < 2 ? h0 ^ c[3] ^ k1 : xor3(h0, c[3], k1);
     c[0] = n0;
     c[1] = (uint32_t)p1;
     c[2] = n2;
