@@ -2,8 +2,8 @@
 //
 // The paper compares its closed forms with the correlated Gaussian model of
 // prior work, sampled by Monte Carlo (Sec. 5.2: 1000 samples; Sec. 5.3: 2000
-// samples).  Here each vertex owns one wave64; lane l takes samples l, l+64,
-// ...; the stencil's mean and Cholesky factor are wave-uniform.
+// samples).  Here a wave64 owns a vertex (or two); lane l takes samples l,
+// l+64, ....
 //
 // Sample i of vertex (y, x): Philox4x32-10 with counter (i, y*W+x, field_id,
 // b) and key (seed lo, seed hi); the four words of block b = 0 give uniforms
@@ -27,14 +27,10 @@ namespace cp {
 
 namespace {
 
-__device__ __forceinline__ float u24(uint32_t r) { return u24_of<float>(r); }
-
-
-template <typename V>
-__device__ __forceinline__ V wave_sum(V v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// ((word >> 8) + 1/2) 2^-24 in one fused multiply-add (scaling by a power of
+// two is exact: the same value as u24_of<float>)
+__device__ __forceinline__ float u24(uint32_t r) {
+  return __builtin_fmaf((float)(r >> 8), 5.9604644775390625e-8f, 2.98023223876953125e-8f);
 }
 
 struct MvgArgs {
@@ -45,86 +41,196 @@ struct MvgArgs {
   const float* gmax;
   double* grad;
   double* jmu;  // [5][H][W] workspace (adjoint)
-  int H, W, ns, est;
+  int H, W, ns;
   int64_t rs, ps;
   uint32_t k0, k1, fid;
 };
 
-// Wave-uniform stencil in the vertex's local frame (origin mu_v).
+// The neighbours' values of a sample, a contraction of four rows of L with the
+// sample's deviates, on the matrix cores.  v_mfma_f32_4x4x1 forms
+// D[i][j] += A[i] B[j] in each of its 16 blocks of four lanes: with lane l
+// holding row l mod 4 of the left matrix and its own sample's z_k as B, lane l
+// receives the four values of its own sample.  The four instructions
+// (k = 0..3) issue beside the vector unit, which this kernel keeps busy: 1.61
+// against 1.81 ms with the 16 fused multiply-adds (500^2 x 2000).
+//
+// DIFF (the estimators): rows L_nk - L_4k, so the values are x_n - c,
+// differenced in FP64 and rounded once, with the deviates' kDeviateScale.
+// A row whose neighbour is absent repeats the first present one, which leaves
+// minimum and maximum as they are; without any neighbour all rows are +inf.
+//
+// Otherwise (the adjoint) the rows of L: each value is then the chain of FP32
+// fused multiply-adds mu_n - mu_v + L_n0 z_0 + ... in the order of k.  A row
+// whose neighbour is absent is NaN, which minimum and maximum skip.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 struct MvgStencil {
-  float d[4];      // mu_n - mu_v
-  float L[15];     // packed lower triangle over (e, n, w, s, v)
-  bool pres[4];
-  float iL44;
+  float row[4];  // lane l: row of neighbour l mod 4
+  f32x4 d;       // mu_n - mu_v (wave-uniform)
+  float L44;
+  int first;      // first present neighbour, 4: none
 };
 
-__device__ __forceinline__ void load_stencil(const MvgArgs& a, int y, int x, MvgStencil& s) {
+template <bool DIFF>
+__device__ __forceinline__ void load_stencil(const MvgArgs& a, int v, int lane, MvgStencil& s) {
+  const int y = v / a.W, x = v - y * a.W;
   const int64_t at = (int64_t)y * a.rs + x;
   const double mv = a.par[at];
-  const int dy[4] = {0, -1, 0, 1}, dx[4] = {1, 0, -1, 0};
+  const bool pres[4] = {x + 1 < a.W, y > 0, x > 0, y + 1 < a.H};
+  const int64_t off[4] = {1, -a.rs, -1, a.rs};
+  float d0 = __builtin_inff();
+  s.first = 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int yy = y + dy[i], xx = x + dx[i];
-    s.pres[i] = yy >= 0 && yy < a.H && xx >= 0 && xx < a.W;
-    s.d[i] = s.pres[i] ? (float)(a.par[(int64_t)yy * a.rs + xx] - mv) : 0.0f;
+  for (int i = 3; i >= 0; --i) {
+    s.d[i] = pres[i] ? (float)(a.par[at + off[i]] - mv) : 0.0f;
+    d0 = pres[i] ? s.d[i] : d0;
+    s.first = pres[i] ? i : s.first;
   }
 #pragma unroll
-  for (int k = 0; k < 15; ++k) s.L[k] = (float)a.par[(int64_t)(1 + k) * a.ps + at];
-  s.iL44 = 1.0f / s.L[14];
+  for (int i = 0; i < 4; ++i) s.d[i] = pres[i] ? s.d[i] : DIFF ? d0 : __builtin_nanf("");
+  const int own = lane & 3;
+  const bool has = own == 0 ? pres[0] : own == 1 ? pres[1] : own == 2 ? pres[2] : pres[3];
+  const int n = has ? own : DIFF ? s.first : 4;
+  const double* L = a.par + a.ps + at;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double l = k <= n && n < 4 ? L[(int64_t)(n * (n + 1) / 2 + k) * a.ps] : 0.0;
+    s.row[k] = DIFF ? (float)((l - L[(int64_t)(10 + k) * a.ps]) * (double)kDeviateScale) : (float)l;
+  }
+  s.L44 = (float)L[14 * a.ps];
 }
 
-// x_n (local) for the four neighbours and the conditional mean c of v
-__device__ __forceinline__ void stencil_values(const MvgStencil& s, const float z[4], float xn[4], float& c) {
-  const float* L = s.L;
-  xn[0] = s.d[0] + L[0] * z[0];
-  xn[1] = s.d[1] + L[1] * z[0] + L[2] * z[1];
-  xn[2] = s.d[2] + L[3] * z[0] + L[4] * z[1] + L[5] * z[2];
-  xn[3] = s.d[3] + L[6] * z[0] + L[7] * z[1] + L[8] * z[2] + L[9] * z[3];
-  c = L[10] * z[0] + L[11] * z[1] + L[12] * z[2] + L[13] * z[3];
+__device__ __forceinline__ f32x4 stencil_values(const MvgStencil& s, const float (&z)[4]) {
+  f32x4 r = s.d;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) r = __builtin_amdgcn_mfma_f32_4x4x1f32(s.row[k], z[k], r, 0, 0, 0);
+  return r;
 }
 
+__device__ __forceinline__ float min4(const f32x4& v) {
+  return __builtin_fminf(__builtin_fminf(__builtin_fminf(v[0], v[1]), v[2]), v[3]);
+}
+__device__ __forceinline__ float max4(const f32x4& v) {
+  return __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(v[0], v[1]), v[2]), v[3]);
+}
+
+// sum over the 16 lanes of a row, in every lane of it
+__device__ __forceinline__ double row_sum(double v) {
+#define CP_ROW_STEP(CTRL)                                                                               \
+  {                                                                                                     \
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);                                                 \
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);               \
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);       \
+    v += __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);                                           \
+  }
+  CP_ROW_STEP(0xB1)   // quad_perm: lane ^ 1
+  CP_ROW_STEP(0x4E)   // quad_perm: lane ^ 2
+  CP_ROW_STEP(0x141)  // row_half_mirror
+  CP_ROW_STEP(0x140)  // row_mirror
+#undef CP_ROW_STEP
+  return v;
+}
+
+// Two sums at once: lanes of the lower half (SWAP 32) or of the even rows
+// (SWAP 16) receive a's partial sums, the others b's.
+template <int SWAP>
+__device__ __forceinline__ double pair_sum(double a, double b) {
+  const uint64_t p = __builtin_bit_cast(uint64_t, a), q = __builtin_bit_cast(uint64_t, b);
+  uint64_t r[2] = {0, 0};
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const uint32_t x = (uint32_t)(p >> 32 * w), y = (uint32_t)(q >> 32 * w);
+    const auto t = SWAP == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                              : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    r[0] |= (uint64_t)(uint32_t)t[0] << 32 * w;
+    r[1] |= (uint64_t)(uint32_t)t[1] << 32 * w;
+  }
+  return __builtin_bit_cast(double, r[0]) + __builtin_bit_cast(double, r[1]);
+}
+
+// One wave owns V vertices and takes the samples i = lane, lane + 64, ... of
+// each: the first rounds of their Philox blocks, as far as they depend on the
+// sample alone, are formed once (500^2 x 2000, V = 1: 1.71 ms, 2: 1.61, 4:
+// 1.73).
+//
+// Bound by vector issue: 105 instructions a sample, 36 of them the generator's,
+// ten transcendental (eight cycles each).  500^2 x 2000: 1.71 -> 1.53 ms.  With q the upper tail of |r|,
+// Phi(r) = [r >= 0] - copysign(q, r): the first part is counted by the scalar
+// unit, and q is summed with its full relative precision.
+template <int V, bool HIT>
 __global__ __launch_bounds__(256) void k_mvg_fwd(MvgArgs a) {
   const int lane = threadIdx.x & 63;
-  const int v = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (v >= a.H * a.W) return;
-  const int y = v / a.W, x = v - y * a.W;
-  MvgStencil s;
-  load_stencil(a, y, x, s);
-  double smin = 0.0, smax = 0.0;
-  for (int i = lane; i < a.ns; i += 64) {
-    uint32_t c0[4] = {(uint32_t)i, (uint32_t)v, a.fid, 0u};
-    philox(c0, a.k0, a.k1);
-    float z[4];
-    box_muller(u24(c0[0]), u24(c0[1]), z[0], z[1]);
-    box_muller(u24(c0[2]), u24(c0[3]), z[2], z[3]);
-    float xn[4], cm;
-    stencil_values(s, z, xn, cm);
-    float lo = __builtin_inff(), hi = -__builtin_inff();
+  const int v0 = __builtin_amdgcn_readfirstlane((blockIdx.x * 4 + (threadIdx.x >> 6)) * V);
+  const int nv = a.H * a.W;
+  if (v0 >= nv) return;
+  const PhiloxKeys keys = philox_keys(a.k0, a.k1);
+  MvgStencil s[V];
+  float inv[V], invm[V];
+  double qmin[V], qmax[V];
+  int nmin[V], nmax[V];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s.pres[k]) {
-        lo = fminf(lo, xn[k]);
-        hi = fmaxf(hi, xn[k]);
-      }
-    if (a.est == CP_MC_HIT) {
-      uint32_t c1[4] = {(uint32_t)i, (uint32_t)v, a.fid, 1u};
-      philox(c1, a.k0, a.k1);
-      float z4, z5;
-      box_muller(u24(c1[0]), u24(c1[1]), z4, z5);
-      const float xv = cm + s.L[14] * z4;
-      smin += xv < lo ? 1.0 : 0.0;
-      smax += xv > hi ? 1.0 : 0.0;
-    } else {
-      smin += (double)phi_cdf((lo - cm) * s.iL44);
-      smax += (double)phi_cdf((cm - hi) * s.iL44);
-    }
+  for (int u = 0; u < V; ++u) {
+    load_stencil<true>(a, min(v0 + u, nv - 1), lane, s[u]);
+    // r in upper_tail's scale; without neighbours both rows' extremes are +inf
+    // and both estimates 1
+    inv[u] = kTailScale / s[u].L44;
+    invm[u] = s[u].first < 4 ? -inv[u] : inv[u];
+    qmin[u] = qmax[u] = 0.0;
+    nmin[u] = nmax[u] = 0;
   }
-  smin = wave_sum(smin);
-  smax = wave_sum(smax);
-  if (lane == 0) {
-    const int64_t at = (int64_t)y * a.rs + x;
-    a.pmin[at] = (float)(smin / (double)a.ns);
-    a.pmax[at] = (float)(smax / (double)a.ns);
+  // (in a vector register, for the full-rate form)
+  uint32_t sign = 0x80000000u;
+  asm volatile("" : "+v"(sign));
+  const auto add = [&](float r, bool on, int& n, double& q) {
+    // copysign(q, r) in one full-rate instruction (q >= 0, or NaN)
+    const float t = __builtin_bit_cast(
+        float, __builtin_amdgcn_bitop3_b32(__builtin_bit_cast(uint32_t, upper_tail7(r)),
+                                           __builtin_bit_cast(uint32_t, r), sign, 0xF8));
+    n += __popcll(__ballot(on && __builtin_bit_cast(int, r) >= 0));
+    q += (double)(on ? t : 0.0f);
+  };
+  const auto sample = [&](int i, bool on) {
+    float z[V][4];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      uint32_t c[4] = {(uint32_t)i, (uint32_t)(v0 + u), a.fid, 0u};
+      philox(c, keys);
+      box_muller_scaled(u24(c[0]), u24(c[1]), z[u][0], z[u][1]);
+      box_muller_scaled(u24(c[2]), u24(c[3]), z[u][2], z[u][3]);
+    }
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const f32x4 x = stencil_values(s[u], z[u]);
+      const float lo = min4(x), hi = max4(x);
+      if constexpr (HIT) {
+        uint32_t c1[4] = {(uint32_t)i, (uint32_t)(v0 + u), a.fid, 1u};
+        philox(c1, keys);
+        float z4, z5;
+        box_muller(u24(c1[0]), u24(c1[1]), z4, z5);
+        const float t = s[u].L44 * z4;
+        nmin[u] += __popcll(__ballot(on && t < lo));
+        nmax[u] += __popcll(__ballot(on && t > (s[u].first < 4 ? hi : -hi)));
+      } else {
+        add(lo * inv[u], on, nmin[u], qmin[u]);
+        add(hi * invm[u], on, nmax[u], qmax[u]);
+      }
+    }
+  };
+  const int full = a.ns & ~63;
+  for (int i0 = 0; i0 < full; i0 += 64) sample(i0 + lane, true);
+  if (full < a.ns) sample(full + lane, full + lane < a.ns);
+#pragma unroll
+  for (int u = 0; u < V; ++u) {
+    double t = 0.0;
+    if constexpr (!HIT) {
+      // lanes 0..31: minimum, 32..63: maximum
+      t = pair_sum<32>(qmin[u], qmax[u]);
+      t = row_sum(pair_sum<16>(t, t));
+    }
+    if (v0 + u < nv && (lane & 31) == 0) {
+      const int v = v0 + u, y = v / a.W, x = v - y * a.W;
+      (lane ? a.pmax : a.pmin)[(int64_t)y * a.rs + x] =
+          (float)(((double)(lane ? nmax[u] : nmin[u]) - t) / (double)a.ns);
+    }
   }
 }
 
@@ -134,78 +240,115 @@ __global__ __launch_bounds__(256) void k_mvg_fwd(MvgArgs a) {
 // maximum mirrors it.  L is local to the stencil (written directly); the
 // mean plane is shared by five stencils, so its per-stencil partials go to a
 // workspace and a second kernel gathers them.
+//
+// Bound by vector issue: 138 instructions a sample, and about 400 a wave before
+// and after them (512^2 x 1000: 1.04 -> 1.01 ms; the 20 sums over the wave took
+// six shuffles each before, now four values share a register after two).
+//
+// A chain of FP32 sums per lane, so the order and the rounding of every
+// operation of a sample are part of the result.
 __global__ __launch_bounds__(256) void k_mvg_bwd(MvgArgs a) {
   const int lane = threadIdx.x & 63;
   const int v = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   if (v >= a.H * a.W) return;
   const int y = v / a.W, x = v - y * a.W;
+  const PhiloxKeys keys = philox_keys(a.k0, a.k1);
   MvgStencil s;
-  load_stencil(a, y, x, s);
+  load_stencil<false>(a, v, lane, s);
   const int64_t at = (int64_t)y * a.rs + x;
-  const float gmn = a.gmin[at] * s.iL44, gmx = a.gmax[at] * s.iL44;
-  float dmu[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  float dl[15];
+  float L4[4];
 #pragma unroll
-  for (int k = 0; k < 15; ++k) dl[k] = 0.f;
-  for (int i = lane; i < a.ns; i += 64) {
+  for (int k = 0; k < 4; ++k) L4[k] = (float)a.par[(int64_t)(11 + k) * a.ps + at];
+  const float iL44 = 1.0f / s.L44;
+  const float gmn = a.gmin[at] * iL44, gmx = a.gmax[at] * iL44;
+  // sums 0..4: mean of v, e, n, w, s; 5 + k: entry k of L
+  float acc[20];
+#pragma unroll
+  for (int k = 0; k < 20; ++k) acc[k] = 0.f;
+  const auto sample = [&](int i, bool on) {
     uint32_t c0[4] = {(uint32_t)i, (uint32_t)v, a.fid, 0u};
-    philox(c0, a.k0, a.k1);
+    philox(c0, keys);
     float z[4];
     box_muller(u24(c0[0]), u24(c0[1]), z[0], z[1]);
     box_muller(u24(c0[2]), u24(c0[3]), z[2], z[3]);
-    float xn[4], cm;
-    stencil_values(s, z, xn, cm);
-    float lo = __builtin_inff(), hi = -__builtin_inff();
-    int amin = -1, amax = -1;
+    const f32x4 xn = stencil_values(s, z);
+    const float cm = fmaf(L4[3], z[3], fmaf(L4[2], z[2], fmaf(L4[0], z[0], L4[1] * z[1])));
+    const float lo = min4(xn), hi = max4(xn);
+    const float rmin = (lo - cm) * iL44, rmax = (cm - hi) * iL44;
+    const float px = phi_pdf(rmax);
+    const float gm = on ? gmn * phi_pdf(rmin) : 0.f, gx = on ? gmx * px : 0.f;
+    const float c4 = on ? fmaf(gmx, px, -gm) : 0.f;
+    // the first neighbour that attains the extreme takes it
+    float cr[4], rm = gm, rx = gx;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s.pres[k]) {
-        if (amin < 0 || xn[k] < lo) {
-          lo = xn[k];
-          amin = k;
-        }
-        if (amax < 0 || xn[k] > hi) {
-          hi = xn[k];
-          amax = k;
-        }
+    for (int r = 0; r < 3; ++r) {
+      const bool im = xn[r] == lo, ix = xn[r] == hi;
+      cr[r] = (im ? rm : 0.f) - (ix ? rx : 0.f);
+      rm = im ? 0.f : rm;
+      rx = ix ? 0.f : rx;
+    }
+    cr[3] = rm - rx;
+    acc[0] += c4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[1 + r] += cr[r];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int k = 0; k <= r; ++k) acc[5 + r * (r + 1) / 2 + k] = fmaf(cr[r], z[k], acc[5 + r * (r + 1) / 2 + k]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[15 + j] = fmaf(c4, z[j], acc[15 + j]);
+    acc[19] -= on ? fmaf(gx, rmax, gm * rmin) : 0.f;
+  };
+  // The first neighbour keeps both extremes if its values are NaN; without
+  // neighbours the estimate is the constant 1.
+  bool nan = false;
+  const float any = ((s.d[0] + s.d[1]) + (s.d[2] + s.d[3])) + ((s.row[0] + s.row[1]) + (s.row[2] + s.row[3]));
+  if (__ballot(any != any)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      bool is = s.d[r] != s.d[r];
+#pragma unroll
+      for (int k = 0; k <= r; ++k) {
+        const float l = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s.row[k]), r));
+        is = is || l != l;
       }
-    if (amin < 0) continue;  // no neighbours: the estimate is the constant 1
-    const float rmin = (lo - cm) * s.iL44, rmax = (cm - hi) * s.iL44;
-    const float gm = gmn * phi_pdf(rmin), gx = gmx * phi_pdf(rmax);
-    float cr[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) cr[r] = (amin == r ? gm : 0.f) - (amax == r ? gx : 0.f);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dmu[1 + r] += cr[r];
-    dmu[0] += gx - gm;
-    // rows 0..3 (packed offsets 0, 1, 3, 6)
-    dl[0] = fmaf(cr[0], z[0], dl[0]);
-    dl[1] = fmaf(cr[1], z[0], dl[1]);
-    dl[2] = fmaf(cr[1], z[1], dl[2]);
-    dl[3] = fmaf(cr[2], z[0], dl[3]);
-    dl[4] = fmaf(cr[2], z[1], dl[4]);
-    dl[5] = fmaf(cr[2], z[2], dl[5]);
-    dl[6] = fmaf(cr[3], z[0], dl[6]);
-    dl[7] = fmaf(cr[3], z[1], dl[7]);
-    dl[8] = fmaf(cr[3], z[2], dl[8]);
-    dl[9] = fmaf(cr[3], z[3], dl[9]);
-    const float c4 = gx - gm;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dl[10 + j] = fmaf(c4, z[j], dl[10 + j]);
-    dl[14] -= gm * rmin + gx * rmax;
+      nan = nan || (s.first == r && is);
+    }
   }
-  const double inv = 1.0 / (double)a.ns;
-  double out[20];
+  if (nan) {
+    const float bad = __builtin_nanf("");
+    acc[0] = bad;
 #pragma unroll
-  for (int k = 0; k < 5; ++k) out[k] = wave_sum((double)dmu[k]);
+    for (int r = 0; r < 4; ++r) {
+      if (s.first != r) continue;
+      acc[1 + r] = bad;
 #pragma unroll
-  for (int k = 0; k < 15; ++k) out[5 + k] = wave_sum((double)dl[k]);
-  if (lane == 0) {
-    const int64_t plane = (int64_t)a.H * a.W, id = v;
+      for (int k = 0; k <= r; ++k) acc[5 + r * (r + 1) / 2 + k] = bad;
+    }
 #pragma unroll
-    for (int k = 0; k < 5; ++k) a.jmu[k * plane + id] = out[k] * inv;
+    for (int k = 15; k < 20; ++k) acc[k] = bad;
+  } else if (s.first < 4) {
+    const int full = a.ns & ~63;
+    for (int i0 = 0; i0 < full; i0 += 64) sample(i0 + lane, true);
+    if (full < a.ns) sample(full + lane, full + lane < a.ns);
+  }
+  // 20 sums over the wave, four to a register: row q of register m holds sum
+  // 4 m + {0, 2, 1, 3}[q]
+  const double inv_ns = 1.0 / (double)a.ns;
+  const int64_t plane = (int64_t)a.H * a.W;
+  const int q = lane >> 4, slot = (q & 1) * 2 + (q >> 1);
 #pragma unroll
-    for (int k = 0; k < 15; ++k) a.grad[(int64_t)(1 + k) * a.ps + at] = out[5 + k] * inv;
+  for (int m = 0; m < 5; ++m) {
+    const double p0 = pair_sum<32>((double)acc[4 * m], (double)acc[4 * m + 1]);
+    const double p1 = pair_sum<32>((double)acc[4 * m + 2], (double)acc[4 * m + 3]);
+    const double t = row_sum(pair_sum<16>(p0, p1)) * inv_ns;
+    const int k = 4 * m + slot;
+    if ((lane & 15) == 0) {
+      if (k < 5)
+        a.jmu[k * plane + v] = t;
+      else
+        a.grad[(int64_t)(k - 4) * a.ps + at] = t;
+    }
   }
 }
 
@@ -228,10 +371,13 @@ __global__ __launch_bounds__(256) void k_philox_raw(int64_t n, const uint32_t* c
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   uint32_t c[4] = {ctr[4 * i], ctr[4 * i + 1], ctr[4 * i + 2], ctr[4 * i + 3]};
-  philox(c, k0, k1);
+  philox(c, philox_keys(k0, k1));
 #pragma unroll
   for (int k = 0; k < 4; ++k) out[4 * i + k] = c[k];
 }
+
+// two vertices per wave once that still leaves four waves per SIMD
+constexpr int64_t kMvgPairVertices = 8192;
 
 MvgArgs make_args(const Field& f, const double* params) {
   MvgArgs a{};
@@ -239,7 +385,6 @@ MvgArgs make_args(const Field& f, const double* params) {
   a.H = f.H;
   a.W = f.W;
   a.ns = f.ns;
-  a.est = f.est;
   a.rs = f.rs;
   a.ps = f.plane();
   a.k0 = (uint32_t)f.seed;
@@ -255,7 +400,19 @@ hipError_t mvg_forward(const Field& f, const double* params, float* pmin, float*
   a.pmin = pmin;
   a.pmax = pmax;
   const int64_t nv = (int64_t)f.H * f.W;
-  hipLaunchKernelGGL(k_mvg_fwd, dim3((unsigned)((nv + 3) / 4)), dim3(256), 0, st, a);
+  const bool two = nv >= kMvgPairVertices;
+  const dim3 grid((unsigned)((nv + (two ? 8 : 4) - 1) / (two ? 8 : 4))), block(256);
+  if (f.est == CP_MC_HIT) {
+    if (two)
+      hipLaunchKernelGGL((k_mvg_fwd<2, true>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((k_mvg_fwd<1, true>), grid, block, 0, st, a);
+  } else {
+    if (two)
+      hipLaunchKernelGGL((k_mvg_fwd<2, false>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((k_mvg_fwd<1, false>), grid, block, 0, st, a);
+  }
   return hipGetLastError();
 }
 

@@ -20,24 +20,40 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// Ten rounds on the counter c in place, key (k0, k1).  Each round's two
-// 32 x 32 -> 64-bit products are formed whole (one v_mad_u64_u32 each rather
-// than a high and a low multiply: a third faster on gfx950).
-__device__ __forceinline__ void philox(uint32_t c[4], uint32_t k0, uint32_t k1) {
+// The key words of the ten rounds.  In vector registers: gfx950 issues the
+// plain FP32 and 32-bit logical instructions every two cycles, but every four
+// where one operand is a scalar register.  The first two rounds' words are
+// mostly wave-uniform in the samplers and stay with the scalar unit.  VEC =
+// false (where registers are short): all in scalar registers.
+struct PhiloxKeys {
+  uint32_t a[10], b[10];
+};
+template <bool VEC = true>
+__device__ __forceinline__ PhiloxKeys philox_keys(uint32_t k0, uint32_t k1) {
+  PhiloxKeys k;
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    k.a[r] = k0 + (uint32_t)r * kPhiloxW0;
+    k.b[r] = k1 + (uint32_t)r * kPhiloxW1;
+    if (VEC && r >= 2) asm volatile("" : "+v"(k.a[r]), "+v"(k.b[r]));
+  }
+  return k;
+}
+
+// Ten rounds on the counter c in place.  Each round's two 32 x 32 -> 64-bit
+// products are formed whole (one v_mad_u64_u32 each rather than a high and a
+// low multiply: a third faster on gfx950).
+__device__ __forceinline__ void philox(uint32_t c[4], const PhiloxKeys& k) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)kPhiloxM0 * c[0], p1 = (uint64_t)kPhiloxM1 * c[2];
-    // (the first two rounds' words are mostly wave-uniform in the samplers:
-    // left to the scalar unit)
     const uint32_t h1 = (uint32_t)(p1 >> 32), h0 = (uint32_t)(p0 >> 32);
-    const uint32_t n0 = r < 2 ? h1 ^ c[1] ^ k0 : xor3(h1, c[1], k0);
-    const uint32_t n2 = r < 2 ? h0 ^ c[3] ^ k1 : xor3(h0, c[3], k1);
+    const uint32_t n0 = r < 2 ? h1 ^ c[1] ^ k.a[r] : xor3(h1, c[1], k.a[r]);
+    const uint32_t n2 = r < 2 ? h0 ^ c[3] ^ k.b[r] : xor3(h0, c[3], k.b[r]);
     c[0] = n0;
     c[1] = (uint32_t)p1;
     c[2] = n2;
     c[3] = (uint32_t)p0;
-    k0 += kPhiloxW0;
-    k1 += kPhiloxW1;
   }
 }
 

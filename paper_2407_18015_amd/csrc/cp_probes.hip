@@ -33,10 +33,11 @@ __global__ __launch_bounds__(256) void k_mc_ceiling(int nv, int ns, uint32_t k0,
   const int lane = threadIdx.x & 63;
   const int v = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   if (v >= nv) return;
+  const cp::PhiloxKeys keys = cp::philox_keys(k0, k1);
   double a = 0.0, b = 0.0;
   for (int i = lane; i < ns; i += 64) {
     uint32_t c[4] = {(uint32_t)i, (uint32_t)v, fid, 0u};
-    cp::philox(c, k0, k1);
+    cp::philox(c, keys);
     float z[4];
     cp::box_muller(cp::u24_of<float>(c[0]), cp::u24_of<float>(c[1]), z[0], z[1]);
     cp::box_muller(cp::u24_of<float>(c[2]), cp::u24_of<float>(c[3]), z[2], z[3]);
@@ -45,8 +46,8 @@ __global__ __launch_bounds__(256) void k_mc_ceiling(int nv, int ns, uint32_t k0,
       a += (double)cp::phi_pdf(r0);
       b += (double)cp::phi_pdf(r1);
     } else {
-      a += (double)cp::phi_cdf(r0);
-      b += (double)cp::phi_cdf(r1);
+      a += (double)cp::upper_tail7(r0);
+      b += (double)cp::upper_tail7(r1);
     }
   }
   a = wave_sum(a);

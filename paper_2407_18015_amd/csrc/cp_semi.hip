@@ -97,6 +97,7 @@ __global__ __launch_bounds__(kFwdTX* TY) void k_semi(SemiArgs<T> a, int tiles_x,
     }
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     const uint32_t at = (uint32_t)((int64_t)y * a.W + x);
+    const PhiloxKeys keys = philox_keys<false>(a.k0, a.k1);
     uint32_t w[4] = {0u, 0u, 0u, 0u};
     for (int i = 0; i < a.ns; ++i) {
       if ((i & 3) == 0) {
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kFwdTX* TY) void k_semi(SemiArgs<T> a, int tiles_x,
         w[1] = at;
         w[2] = a.fid;
         w[3] = 2u;
-        philox(w, a.k0, a.k1);
+        philox(w, keys);
       }
       const A r = u24_of<A>(w[i & 3]) * (A)Tv;
       int j = 0;
