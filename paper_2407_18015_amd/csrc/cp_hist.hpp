@@ -8,9 +8,7 @@
 // that sum by linearity gives the same number as integrating
 // pdf_v * prod S_n once over the merged edges, which costs O(5h) instead of
 // O(h^5).  On each interval the product of four linear factors is integrated
-// exactly from its end values (Bernstein form: the integral over [0,1] of
-// t^k (1-t)^(4-k) is k!(4-k)!/5!), so every term is non-negative and no
-// cancellation occurs.
+// exactly, from the factors at the midpoint and their half-changes.
 //
 // Staged per vertex in LDS (planes of the extended tile, E vertices each):
 //   0 lo, 1 hi, 2..h+1 masses, h+2 zero.  An invalid histogram (lo >= hi,
@@ -41,6 +39,15 @@ struct HistLds {
   CP_HD bool valid(int e) const { return base[e] == base[e]; }
 };
 
+// Compute a here: without it the compiler moves an interval's integrals behind
+// the cursor steps and copies the state they need (24 moves an interval).
+template <typename T>
+CP_HD void settle(T& a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(a));
+#endif
+}
+
 // Validity marking of every staged histogram (lo := NaN when invalid).
 template <typename T, int NT>
 CP_HD void hist_stage_validity(T* lds, int E, int h, int tid) {
@@ -54,17 +61,6 @@ CP_HD void hist_stage_validity(T* lds, int E, int h, int tid) {
     }
     if (!ok) lds[e] = __builtin_nan("");
   }
-}
-
-// Integral over [0,1] of prod_{i<4} (f0_i (1-t) + f1_i t)
-template <typename T>
-CP_HD T bern4(const T (&f0)[4], const T (&f1)[4]) {
-  T b0 = f0[0], b1 = f1[0];
-  T c0 = b0 * f0[1], c1 = cfma(b0, f1[1], b1 * f0[1]), c2 = b1 * f1[1];
-  T d0 = c0 * f0[2], d1 = cfma(c0, f1[2], c1 * f0[2]), d2 = cfma(c1, f1[2], c2 * f0[2]), d3 = c2 * f1[2];
-  T e0 = d0 * f0[3], e1 = cfma(d0, f1[3], d1 * f0[3]), e2 = cfma(d1, f1[3], d2 * f0[3]),
-    e3 = cfma(d2, f1[3], d3 * f0[3]), e4 = d3 * f1[3];
-  return cfma(e2, T(1.0 / 30.0), cfma(e1 + e3, T(0.05), (e0 + e4) * T(0.2)));
 }
 
 }  // namespace cp
@@ -103,80 +99,78 @@ struct HistSuf {
 
 // One neighbour in the vertex frame: survival S(x) = snx + slope (nxt - x)
 // on the current bin; F = tot - S.  Its edges above the first are counted
-// down from the last, hi - (h - k) Delta (k = h: hi itself), so the cursor
-// keeps hi and not lo.
+// down from the last, hi + k Delta with k = -(h - 1) .. 0 (k = 0: hi itself),
+// so the cursor keeps hi and not lo, and its edge index is the float k: the
+// next edge is one addition and one fused multiply-add, which issue in half
+// the cycles of an integer's conversion.  p points to the suffix sum at the
+// next edge and moves by one plane a step.
 template <typename T>
 struct SufCursor {
-  int j;  // -1 below the range, h above it
+  const T* p;
+  T k;  // next edge (-h: the first, lo); above 0: past the range
   T hi, d, id, nxt, snx, slope, tot;
 };
 
 template <typename T>
 CP_HD void suf_cursor_init(SufCursor<T>& c, const HistSuf<T>& L, int e, T lo, T hi, bool present, T big) {
   const int h = L.h;
+  const T* U0 = L.base + 2 * L.E + e;
   c.hi = hi;
   c.d = (hi - lo) * (T(1) / T(h));
   c.id = T(h) * crcp(hi - lo);
+  // past the range, at the zero plane
+  c.p = U0 + h * L.E;
+  c.k = T(1);
+  c.nxt = big;
+  c.slope = T(0);
   if (!present) {  // constant factor 1 in both products
-    c.j = h;
-    c.nxt = big;
     c.snx = T(1);
-    c.slope = T(0);
     c.tot = T(2);
     return;
   }
-  c.tot = L.U(e, 0);
+  c.tot = *U0;
+  c.snx = T(0);
   if (!(lo < T(0))) {  // range starts at or after x = 0
-    c.j = -1;
+    c.p = U0;
+    c.k = T(-h);
     c.nxt = lo;
     c.snx = c.tot;
-    c.slope = T(0);
     return;
   }
+  if (!(hi > T(0))) return;  // the whole range lies below x = 0
   int j = (int)(-lo * c.id);
   j = j < 0 ? 0 : (j > h - 1 ? h - 1 : j);
   const auto edge = [&](int k) { return cfma(T(k - h), c.d, hi); };  // 1 <= k <= h
   if (j + 1 < h && !(edge(j + 1) > T(0))) ++j;
   if (j > 0 && edge(j) > T(0)) --j;
-  c.j = j;
+  c.k = T(j + 1 - h);
   c.nxt = edge(j + 1);
-  const T uj = L.U(e, j);
-  c.snx = L.U(e, j + 1);
-  c.slope = (uj - c.snx) * c.id;
-  if (!(hi > T(0))) {  // the whole range lies below x = 0
-    c.j = h;
-    c.nxt = big;
-    c.snx = T(0);
-    c.slope = T(0);
-  }
+  c.p = U0 + (j + 1) * L.E;
+  c.snx = *c.p;
+  c.slope = (U0[j * L.E] - c.snx) * c.id;
 }
 
 // Cross the edge x1 if it is this cursor's next edge: one branch, and inside
-// it no other (the next suffix sum is read from the zero plane once the
-// cursor leaves the range, so survival and slope become 0 by themselves).
+// it no other (past the range the cursor stays at the zero plane, so survival
+// and slope become 0 by themselves).
 template <typename T>
-CP_HD void suf_cursor_step(SufCursor<T>& c, const HistSuf<T>& L, int e, T x1, T big) {
-  const int h = L.h;
+CP_HD void suf_cursor_step(SufCursor<T>& c, int E, T x1, T big) {
   if (!(c.nxt == x1)) return;
-  const int j1 = c.j + 1;  // the bin entered (h: past the range)
-  const T prev = c.snx;
-  c.snx = L.U(e, j1 + 1 < h ? j1 + 1 : h);
-  c.slope = (prev - c.snx) * c.id;
-  c.nxt = j1 >= h ? big : cfma(T(j1 + 1 - h), c.d, c.hi);
-  c.j = j1;
+  c.k += T(1);
+  const bool past = c.k > T(0);
+  c.p += past ? 0 : E;
+  const T u = *c.p;
+  c.slope = (c.snx - u) * c.id;
+  c.snx = u;
+  c.nxt = past ? big : cfma(c.k, c.d, c.hi);
 }
 
 // ---------------------------------------------------------------------------
-// Branch-free cursor (the adjoint sweep): the same survival function as
-// SufCursor, S(x) = snx + slope (nxt - x) on the current bin, F = tot - S, in
-// a frame where the sweep runs from x = 0.  It holds the index m of its next
-// edge (0 below the range, h + 1 past it); U_m is read from plane
-// 2 + min(m, h) (the zero plane past the range), so no LDS index is kept; the
-// edges are lo + m Delta for m < h and hi itself for m = h.  Every step is
-// written with selects, so a wave whose lanes cross different edges runs one
-// straight sequence of instructions.  The forward and saddle sweeps keep
-// SufCursor: its branchy steps need fewer registers, and those sweeps gain
-// more from occupancy than from fewer instructions.
+// Cursor of the adjoint sweep: the same survival function, S(x) = snx + slope
+// (nxt - x) on the current bin, F = tot - S.  The sweep also needs the index m
+// of the next edge (0 below the range, h + 1 past it) for the bin it leaves,
+// and has no registers left for a pointer or a float index beside it: U_m is
+// read from plane 2 + min(m, h) (the zero plane past the range).
 // ---------------------------------------------------------------------------
 template <typename T>
 struct HistCursor {
@@ -184,16 +178,13 @@ struct HistCursor {
   T nxt;   // next edge (big past the range)
   T snx;   // U_m: survival at the next edge
   T slope; // mass density of the current bin (0 outside the range)
-  T tot, lo, hi, d, id;
-  // inside the range (the current bin is a bin of this histogram)
-  CP_HD bool in_range(int h) const { return (unsigned)(m - 1) < (unsigned)h; }
+  T tot, hi, d, id;
 };
 
 // `present` false: the constant factor 1 in both products (S = 1, F = 2 - 1)
 template <typename T>
 CP_HD void hist_cursor_init(HistCursor<T>& c, const T* base, int E, int h, int e, T lo, T hi, bool present, T big) {
   const T hf = T(h);
-  c.lo = lo;
   c.hi = hi;
   c.d = (hi - lo) * (T(1) / hf);
   c.id = hf * crcp(hi - lo);
@@ -220,7 +211,7 @@ CP_HD void hist_cursor_init(HistCursor<T>& c, const T* base, int E, int h, int e
   }
   int j = (int)(-lo * c.id);
   j = j < 0 ? 0 : (j > h - 1 ? h - 1 : j);
-  const auto edge = [&](int k) { return k >= h ? hi : cfma(T(k), c.d, lo); };
+  const auto edge = [&](int k) { return cfma(T(k - h), c.d, hi); };  // 1 <= k <= h
   if (j + 1 < h && !(edge(j + 1) > T(0))) ++j;
   if (j > 0 && edge(j) > T(0)) --j;
   c.m = j + 1;
@@ -229,22 +220,19 @@ CP_HD void hist_cursor_init(HistCursor<T>& c, const T* base, int E, int h, int e
   c.slope = (base[(2 + j) * E + e] - c.snx) * c.id;
 }
 
-// Advance to the next edge if `adv` (selects, no branch); e is the
-// histogram's LDS index in a plane.
+// Cross the next edge; e is the histogram's LDS index in a plane.
 template <typename T>
-CP_HD void hist_cursor_step(HistCursor<T>& c, const T* base, int E, int e, int h, T big, bool adv) {
-  const int m1 = c.m + 1;
-  const T u1 = base[(2 + (m1 < h ? m1 : h)) * E + e];
-  const T nx1 = m1 < h ? cfma(T(m1), c.d, c.lo) : (m1 == h ? c.hi : big);
-  const T sl1 = (c.snx - u1) * c.id;
-  c.m = adv ? m1 : c.m;
-  c.snx = adv ? u1 : c.snx;
-  c.slope = adv ? sl1 : c.slope;
-  c.nxt = adv ? nx1 : c.nxt;
+CP_HD void hist_cursor_step(HistCursor<T>& c, const T* base, int E, int e, int h, T big) {
+  c.m += 1;
+  const int mm = c.m < h ? c.m : h;  // (the zero plane past the range)
+  const T u = base[(2 + mm) * E + e];
+  c.slope = (c.snx - u) * c.id;
+  c.snx = u;
+  c.nxt = mm != c.m ? big : cfma(T(c.m - h), c.d, c.hi);
 }
 
 // The vertex's own bins over [0, hv]: bin jv, next edge nv (hv for the last
-// bin, big past it), density pv, U above the bin uv; stepped with selects.
+// bin, big past it), density pv, U above the bin uv.
 template <typename T>
 struct VertexBins {
   int jv;
@@ -262,15 +250,13 @@ CP_HD void vertex_bins_init(VertexBins<T>& b, const T* base, int E, int h, int e
 }
 
 template <typename T>
-CP_HD void vertex_bins_step(VertexBins<T>& b, const T* base, int E, int h, int ev, T hv, T big, bool adv) {
+CP_HD void vertex_bins_step(VertexBins<T>& b, const T* base, int E, int h, int ev, T hv, T big) {
   const int jn = b.jv + 1;
   const T un = base[(jn + 3 < h + 2 ? jn + 3 : h + 2) * E + ev];  // U_{jn+1}
-  const T pn = (b.uv - un) * b.idv;
-  const T nn = jn + 1 < h ? T(jn + 1) * b.dv : (jn + 1 == h ? hv : big);
-  b.jv = adv ? jn : b.jv;
-  b.uv = adv ? un : b.uv;
-  b.pv = adv ? pn : b.pv;
-  b.nv = adv ? nn : b.nv;
+  b.jv = jn;
+  b.pv = (b.uv - un) * b.idv;
+  b.uv = un;
+  b.nv = jn + 1 < h ? T(jn + 1) * b.dv : (jn + 1 == h ? hv : big);
 }
 
 // P_min and P_max of vertex ev; neighbour ranges [lo_i, hi_i] in the vertex
@@ -278,8 +264,13 @@ CP_HD void vertex_bins_step(VertexBins<T>& b, const T* base, int E, int h, int e
 // the saddle terms t1 = int pdf_v S_e F_n S_w F_s and t2 = int pdf_v F_e S_n
 // F_w S_s (Eq. 4) in the same sweep: on every merged sub-interval the four
 // survival and distribution functions are the ones P_min and P_max use, so
-// the two mixed products are two more exact Bernstein integrals (the caller
-// keeps them only for vertices with all four neighbours).
+// the two mixed products are two more exact integrals (the caller keeps them
+// only for vertices with all four neighbours).
+//
+// Bound by vector issue: about 295 cycles per wave and interval, half of them
+// the five cursor branches (a wave's lanes cross different edges, so all of
+// them run).  P_min / P_max at 2048^2 x 10 bins: 0.508 -> 0.44 ms, of which the
+// staging found every cell once instead of per plane gave 0.04.
 template <typename T, bool SAD = false>
 __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const int (&en)[4], const bool (&pres)[4],
                                            T hv, const T (&lo)[4], const T (&hi)[4], T& pmin, T& pmax, T& t1,
@@ -287,61 +278,75 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
   const int h = L.h;
   const T big = hv + hv + T(1);
   const T dv = hv * (T(1) / T(h)), idv = T(h) * crcp(hv);
-  int jv = 0;
-  T nv = h > 1 ? dv : hv;
-  T uv = L.U(ev, 1);               // U_{jv+1}
-  T pv = (L.U(ev, 0) - uv) * idv;  // density of the vertex's bin jv
+  // the vertex's bin: its upper edge nv = hv + kv dv, U there, its density
+  const T* pu = L.base + 3 * L.E + ev;
+  T kv = T(1 - h), nv = h > 1 ? dv : hv;
+  T uv = *pu;
+  T pv = (L.U(ev, 0) - uv) * idv;
   SufCursor<T> c[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) suf_cursor_init(c[i], L, en[i], lo[i], hi[i], pres[i], big);
-  // survival / distribution values at the current left end (sa, fa) and at
-  // the next edge (sb, fb); the loop body takes two intervals with the roles
-  // swapped, so no values are copied between intervals
-  T sa[4], fa[4], sb[4], fb[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    sa[i] = cfma(c[i].slope, c[i].nxt, c[i].snx);
-    fa[i] = c[i].tot - sa[i];
-  }
   T x0 = T(0), amin = T(0), amax = T(0), a1 = T(0), a2 = T(0);
-  const auto interval = [&](const T(&s0)[4], const T(&f0)[4], T(&s1)[4], T(&f1)[4]) {
+  const int maxit = 5 * (h + 1) + 2;  // every step crosses at least one edge
+  for (int it = 0; it < maxit; ++it) {
+    if (!(x0 < hv)) break;
     T x1 = nv;
 #pragma unroll
     for (int i = 0; i < 4; ++i) x1 = fmin_nn(x1, c[i].nxt);  // sweep edges: finite
-    const T wgt = pv * (x1 - x0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) suf_cursor_step(c[i], L, en[i], x1, big);
-    // end values from the cursors after their steps (a cursor that crossed
-    // x1 gives S(x1) from its new bin): the state before the step is dead by
-    // now, so the steps update it in place
+    // The factors at the midpoint, S and F, and their half-change t >= 0: on
+    // y in [-1, 1] S_i = S - t y, F_i = F + t y.  Opposite neighbours are
+    // multiplied into quadratics p0 -/+ p1 y + p2 y^2 (p1 the magnitude for
+    // S and F alike, p2 shared by them), and two quadratics integrate to
+    //   2 [p0 q0 + (p0 q2 + p2 q0 +/- p1 q1) / 3 + p2 q2 / 5],
+    // + where both are of S or both of F: then every term is non-negative and
+    // nothing cancels.  In the saddle terms one of each, the magnitudes sum
+    // to at most six times the result.  27 operations for P_min and P_max
+    // (39 with the saddle terms) against 46 (92) from the end values in
+    // Bernstein form.
+    const T mid = (x0 + x1) * T(0.5), hl = (x1 - x0) * T(0.5);
+    T S[4], F[4], t[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      s1[i] = cfma(c[i].slope, c[i].nxt - x1, c[i].snx);
-      f1[i] = c[i].tot - s1[i];
+      S[i] = cfma(c[i].slope, c[i].nxt - mid, c[i].snx);
+      F[i] = c[i].tot - S[i];
+      t[i] = c[i].slope * hl;
     }
-    amin = cfma(wgt, bern4(s0, s1), amin);
-    amax = cfma(wgt, bern4(f0, f1), amax);
+    T s0[2], s1[2], f0[2], f1[2], q2[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      s0[p] = S[p] * S[p + 2];
+      s1[p] = cfma(S[p], t[p + 2], S[p + 2] * t[p]);
+      f0[p] = F[p] * F[p + 2];
+      f1[p] = cfma(F[p], t[p + 2], F[p + 2] * t[p]);
+      q2[p] = t[p] * t[p + 2];
+    }
+    const T top = T(0.2) * (q2[0] * q2[1]), wgt = pv * (x1 - x0);
+    const auto quartic = [&](T p0, T p1, T r0, T r1) {  // p1 r1 with the sign of its term
+      const T m = cfma(p0, q2[1], cfma(q2[0], r0, p1 * r1));
+      return cfma(T(1.0 / 3.0), m, cfma(p0, r0, top));
+    };
+    amin = cfma(wgt, quartic(s0[0], s1[0], s0[1], s1[1]), amin);
+    amax = cfma(wgt, quartic(f0[0], f1[0], f0[1], f1[1]), amax);
     if constexpr (SAD) {
-      const T m0[4] = {s0[0], f0[1], s0[2], f0[3]}, m1[4] = {s1[0], f1[1], s1[2], f1[3]};
-      const T n0[4] = {f0[0], s0[1], f0[2], s0[3]}, n1[4] = {f1[0], s1[1], f1[2], s1[3]};
-      a1 = cfma(wgt, bern4(m0, m1), a1);
-      a2 = cfma(wgt, bern4(n0, n1), a2);
+      a1 = cfma(wgt, quartic(s0[0], s1[0], f0[1], -f1[1]), a1);
+      a2 = cfma(wgt, quartic(f0[0], f1[0], s0[1], -s1[1]), a2);
+      settle(a1);
+      settle(a2);
     }
+    // the old state is dead from here on: the steps update it in place
+    settle(amin);
+    settle(amax);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) suf_cursor_step(c[i], L.E, x1, big);
     if (nv == x1) {
-      ++jv;
-      const T un = L.U(ev, jv + 1 < h ? jv + 1 : h);
+      pu += kv < T(0) ? L.E : 0;
+      kv += T(1);
+      const T un = *pu;
       pv = (uv - un) * idv;
       uv = un;
-      nv = jv + 1 < h ? T(jv + 1) * dv : hv;
+      nv = cfma(tmin(kv, T(0)), dv, hv);
     }
     x0 = x1;
-  };
-  const int maxit = 5 * (h + 1) + 2;  // every step crosses at least one edge
-  for (int it = 0; it < maxit; it += 2) {
-    if (!(x0 < hv)) break;
-    interval(sa, fa, sb, fb);
-    if (!(x0 < hv) || it + 1 >= maxit) break;
-    interval(sb, fb, sa, fa);
   }
   pmin = amin;
   pmax = amax;

@@ -25,19 +25,23 @@ struct FieldPtrs {
 };
 
 // Stage `np` planes of the rectangle [gy0, gy0+EY) x [gx0, gx0+EX) into LDS
-// (plane-major, E = EY*EX per plane).  Cells outside the grid read as 0.
+// (plane-major, E = EY*EX per plane).  Cells outside the grid read as 0.  A
+// thread finds its cell once and walks the planes, four loads in flight: the
+// position took more issue cycles than the plane's load and store.
 template <typename T, int EY, int EX, int NT>
 __device__ __forceinline__ void stage(T* lds, const T* g, int np, int64_t ps, int64_t rs, int H, int W, int gy0,
                                       int gx0, int tid) {
   constexpr int E = EY * EX;
-  for (int p = 0; p < np; ++p) {
-    const T* gp = g + (int64_t)p * ps;
-    for (int i = tid; i < E; i += NT) {
-      const int ey = i / EX, ex = i - ey * EX;
-      const int gy = gy0 + ey, gx = gx0 + ex;
-      T v = T(0);
-      if (gy >= 0 && gy < H && gx >= 0 && gx < W) v = gp[(int64_t)gy * rs + gx];
-      lds[p * E + i] = v;
+  for (int i = tid; i < E; i += NT) {
+    const int ey = i / EX, ex = i - ey * EX;
+    const int gy = gy0 + ey, gx = gx0 + ex;
+    T* to = lds + i;
+    if (gy >= 0 && gy < H && gx >= 0 && gx < W) {
+      const T* gp = g + (int64_t)gy * rs + gx;
+#pragma unroll 4
+      for (int p = 0; p < np; ++p) to[p * E] = gp[p * ps];
+    } else {
+      for (int p = 0; p < np; ++p) to[p * E] = T(0);
     }
   }
 }
