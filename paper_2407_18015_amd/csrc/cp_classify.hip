@@ -59,24 +59,27 @@ __global__ __launch_bounds__(NT) void k_classify_ue(ClassPtrs<T> f, int tiles_x,
     const int en[4] = {e + 1, e - EX, e - 1, e + EX};
     const bool pres[4] = {x + 1 < f.W, y > 0, x > 0, y + 1 < f.H};
     T pmin = T(0), pmax = T(0), t1 = T(0), t2 = T(0);
-    if (!stencil_valid_ue<T, MODEL>(lds, E, e, en, pres)) {
+    T p0, p1, q0[4], q1[4];
+    if (!stencil_load_ue<T, MODEL>(lds, E, e, en, pres, p0, p1, q0, q1)) {
       pmin = pmax = t1 = t2 = qnan<T>();
     } else if constexpr (MODEL == CP_GAUSSIAN) {
-      T mn[4], sn[4], o[4];
+      T o[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        mn[i] = pres[i] ? lds[en[i]] : T(0);
-        sn[i] = pres[i] ? lds[E + en[i]] : T(1);
+        q0[i] = pres[i] ? q0[i] : T(0);
+        q1[i] = pres[i] ? q1[i] : T(1);
       }
-      gauss_vertex<T>(lds[e], lds[E + e], mn, sn, pres, o);
+      gauss_vertex<T>(p0, p1, q0, q1, pres, o);
       pmin = o[0];
       pmax = o[1];
       t1 = o[2];
       t2 = o[3];
-    } else {
+    } else if (!sad) {
       if (mm) vertex_fwd_ue<T, MODEL>(lds, E, e, en, pres, pmin, pmax);
-      // the alternating pattern needs all four neighbours: 0 on the boundary
-      if (sad && pres[0] && pres[1] && pres[2] && pres[3]) vertex_saddle_ue<T, MODEL>(lds, E, e, en, t1, t2);
+    } else if (mm) {
+      vertex_classes_ue<T, MODEL, true>(p0, p1, q0, q1, pres, pmin, pmax, t1, t2);
+    } else {
+      vertex_classes_ue<T, MODEL, false>(p0, p1, q0, q1, pres, pmin, pmax, t1, t2);
     }
     class_store(f, y, x, pmin, pmax, t1, t2);
   }

@@ -106,9 +106,9 @@ template <typename T>
 static hipError_t fwd_typed(const Field& f, const void* params, void* pmin, void* pmax, hipStream_t st) {
   FieldPtrs<T> p = make_ptrs<T>(f, params, pmin, pmax, nullptr, nullptr, nullptr);
   if (f.model == CP_UNIFORM || f.model == CP_EPANECHNIKOV) {
-    // 64 x 16 outputs per 256-thread block, four rows per thread: 79 us
-    // against 87 us for 64 x 4 with one row per thread (Epanechnikov,
-    // 2048^2); grids too small for eight such blocks per CU keep 64 x 4
+    // 64 x 16 outputs per 256-thread block, four rows per thread: 9% faster
+    // than 64 x 4 with one row per thread (Epanechnikov, 2048^2: 65 us);
+    // grids too small for eight such blocks per CU keep 64 x 4
     const int tx = cdiv(f.W, kFwdTX);
     const bool tall = (int64_t)tx * cdiv(f.H, 16) >= kTallTileBlocks;
     const int TYr = tall ? 16 : 4, n = tx * cdiv(f.H, TYr);

@@ -149,6 +149,16 @@ struct GLRem<7> {
 // ---------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------
+// A constant held in a vector register: an FP32 instruction with a modifier
+// cannot carry a literal, and with a scalar register it issues at half rate.
+// (FP64 issues at one rate, and registers are short: left to the compiler.)
+CP_HD inline float vconst(float v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(v));
+#endif
+  return v;
+}
+CP_HD inline double vconst(double v) { return v; }
 template <typename T>
 CP_HD T tmin(T a, T b) {
   return b < a ? b : a;
@@ -161,63 +171,71 @@ CP_HD T tmax(T a, T b) {
 // of a compare and a select)
 CP_HD inline float fmin_nn(float a, float b) { return __builtin_fminf(a, b); }
 CP_HD inline double fmin_nn(double a, double b) { return __builtin_fmin(a, b); }
-template <typename T>
-CP_HD T tclamp(T v, T lo, T hi) {
-  return tmin(tmax(v, lo), hi);
+CP_HD inline float fmax_nn(float a, float b) { return __builtin_fmaxf(a, b); }
+CP_HD inline double fmax_nn(double a, double b) { return __builtin_fmax(a, b); }
+// v clamped to lo <= hi, no NaN: one v_med3_f32 in FP32
+CP_HD inline float clamp_nn(float v, float lo, float hi) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_fmed3f(v, lo, hi);
+#else
+  return fmin_nn(fmax_nn(v, lo), hi);
+#endif
 }
+CP_HD inline double clamp_nn(double v, double lo, double hi) { return fmin_nn(fmax_nn(v, lo), hi); }
+// v clamped to [0, 1]: a modifier of the instruction that produces v
+CP_HD inline float clamp01(float v) { return fmin_nn(fmax_nn(v, 0.0f), 1.0f); }
+CP_HD inline double clamp01(double v) { return fmin_nn(fmax_nn(v, 0.0), 1.0); }
 template <typename T>
 CP_HD T qnan() {
   return __builtin_nan("");
 }
 
-// Compare-exchange of key k with a payload of P values (and an int tag).
+// Selection by a mask of ones or zeros: a < b as a subtraction and a shift,
+// and m ? a : b as one v_bitop3_b32, issue in half the cycles of v_cmp and
+// v_cndmask on gfx950.  Keys are not NaN; equal keys may give either mask.
+CP_HD uint32_t less_mask(float a, float b) {
+  return (uint32_t)(__builtin_bit_cast(int32_t, a - b) >> 31);
+}
+CP_HD uint32_t less_mask(double a, double b) {
+  return (uint32_t)((int32_t)(__builtin_bit_cast(uint64_t, a - b) >> 32) >> 31);
+}
+CP_HD uint32_t sel_bits(uint32_t m, uint32_t a, uint32_t b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA);
+#else
+  return (m & a) | (~m & b);
+#endif
+}
+CP_HD float sel(uint32_t m, float a, float b) {
+  return __builtin_bit_cast(float, sel_bits(m, __builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
+}
+CP_HD double sel(uint32_t m, double a, double b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  return __builtin_bit_cast(double, (uint64_t)sel_bits(m, (uint32_t)(x >> 32), (uint32_t)(y >> 32)) << 32 |
+                                        sel_bits(m, (uint32_t)x, (uint32_t)y));
+}
+
+// Sorting network for four keys (5 comparators), payload follows its key; it
+// records whether each comparator swapped, so that values computed in sorted
+// order can be taken back to neighbour order by unsort4 (the comparators in
+// reverse order, each its own inverse): ten selects per array instead of a
+// select per (slot, neighbour) pair.
 template <typename T, int P>
-CP_HD void cswap(T& ka, T& kb, T (&pa)[P], T (&pb)[P], int& ta, int& tb) {
-  const bool s = kb < ka;
-  T t = s ? kb : ka;
-  kb = s ? ka : kb;
+CP_HD void cswap_rec(T& ka, T& kb, T (&pa)[P], T (&pb)[P], uint32_t& m) {
+  m = less_mask(kb, ka);
+  const T t = sel(m, kb, ka);
+  kb = sel(m, ka, kb);
   ka = t;
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    T u = s ? pb[p] : pa[p];
-    pb[p] = s ? pa[p] : pb[p];
-    pa[p] = u;
-  }
-  int v = s ? tb : ta;
-  tb = s ? ta : tb;
-  ta = v;
-}
-
-// Sorting network for four keys (5 comparators), payload follows its key.
-template <typename T, int P>
-CP_HD void sort4(T (&k)[4], T (&p)[4][P], int (&tag)[4]) {
-  cswap<T, P>(k[0], k[1], p[0], p[1], tag[0], tag[1]);
-  cswap<T, P>(k[2], k[3], p[2], p[3], tag[2], tag[3]);
-  cswap<T, P>(k[0], k[2], p[0], p[2], tag[0], tag[2]);
-  cswap<T, P>(k[1], k[3], p[1], p[3], tag[1], tag[3]);
-  cswap<T, P>(k[1], k[2], p[1], p[2], tag[1], tag[2]);
-}
-
-// The same network, recording whether each comparator swapped, so that
-// values computed in sorted order can be taken back to neighbour order by
-// unsort4 (the comparators in reverse order, each its own inverse): ten
-// selects per array instead of a select per (slot, neighbour) pair.
-template <typename T, int P>
-CP_HD void cswap_rec(T& ka, T& kb, T (&pa)[P], T (&pb)[P], bool& s) {
-  s = kb < ka;
-  T t = s ? kb : ka;
-  kb = s ? ka : kb;
-  ka = t;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    T u = s ? pb[p] : pa[p];
-    pb[p] = s ? pa[p] : pb[p];
+    const T u = sel(m, pb[p], pa[p]);
+    pb[p] = sel(m, pa[p], pb[p]);
     pa[p] = u;
   }
 }
 
 template <typename T, int P>
-CP_HD void sort4_rec(T (&k)[4], T (&p)[4][P], bool (&sw)[5]) {
+CP_HD void sort4_rec(T (&k)[4], T (&p)[4][P], uint32_t (&sw)[5]) {
   cswap_rec<T, P>(k[0], k[1], p[0], p[1], sw[0]);
   cswap_rec<T, P>(k[2], k[3], p[2], p[3], sw[1]);
   cswap_rec<T, P>(k[0], k[2], p[0], p[2], sw[2]);
@@ -226,14 +244,14 @@ CP_HD void sort4_rec(T (&k)[4], T (&p)[4][P], bool (&sw)[5]) {
 }
 
 template <typename T>
-CP_HD void uswap(T& a, T& b, bool s) {
-  const T t = s ? b : a;
-  b = s ? a : b;
+CP_HD void uswap(T& a, T& b, uint32_t m) {
+  const T t = sel(m, b, a);
+  b = sel(m, a, b);
   a = t;
 }
 
 template <typename T>
-CP_HD void unsort4(T (&v)[4], const bool (&sw)[5]) {
+CP_HD void unsort4(T (&v)[4], const uint32_t (&sw)[5]) {
   uswap(v[1], v[2], sw[4]);
   uswap(v[1], v[3], sw[3]);
   uswap(v[0], v[2], sw[2]);
@@ -253,7 +271,7 @@ CP_HD void unsort4(T (&v)[4], const bool (&sw)[5]) {
 // On piece k the integrand (1/Lv) prod_{i<k} (b_i - x)/L_i has degree k:
 // Gauss-Legendre with 1 and 2 nodes is exact for k = 1 and 3; k = 2 and 4
 // take 1 and 2 nodes plus the rule's remainder on the top-degree term (its
-// coefficient the product of the factors' slopes).
+// coefficient the product of the factors' slopes).  k = 4 is the centre.
 // ===========================================================================
 template <typename T>
 struct UniSide {
@@ -261,36 +279,29 @@ struct UniSide {
   T c[4];      // sorted clamped start points
   T b[4];      // matching upper ends
   T iL[4];     // matching 1/(b - a)
-  bool sw[5];  // comparator swaps of the sort (unsort4 restores neighbour order)
+  uint32_t sw[5];  // comparator swaps of the sort (unsort4 restores neighbour order)
   T bmin;
   bool empty;
 };
 
+// an absent neighbour is passed as a = 2 Lv, b = 3 Lv, iL = 1 / Lv: a factor
+// that would start beyond b_min, never active on a non-empty piece
 template <typename T>
-CP_HD void uni_setup(UniSide<T>& s, T Lv, T iLv, const T (&a)[4], const T (&b)[4], const T (&iL)[4],
-                     const bool (&pres)[4]) {
+CP_HD void uni_setup(UniSide<T>& s, T Lv, T iLv, const T (&a)[4], const T (&b)[4], const T (&iL)[4]) {
   s.Lv = Lv;
   s.iLv = iLv;
-  T bmin = Lv;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (pres[i]) bmin = tmin(bmin, b[i]);
-  s.bmin = bmin;
-  s.empty = !(bmin > T(0));
-  T key[4];
+  s.bmin = fmin_nn(fmin_nn(fmin_nn(Lv, b[0]), fmin_nn(b[1], b[2])), b[3]);
+  s.empty = !(s.bmin > T(0));
   T pay[4][2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    // an absent neighbour is a factor that would start at b_min (never
-    // active on a non-empty piece); finite stand-ins keep empty pieces finite
-    key[i] = pres[i] ? tclamp(a[i], T(0), bmin) : bmin;
-    pay[i][0] = pres[i] ? b[i] : T(3) * Lv;
-    pay[i][1] = pres[i] ? iL[i] : iLv;
+    s.c[i] = clamp_nn(a[i], T(0), s.bmin);
+    pay[i][0] = b[i];
+    pay[i][1] = iL[i];
   }
-  sort4_rec<T, 2>(key, pay, s.sw);
+  sort4_rec<T, 2>(s.c, pay, s.sw);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    s.c[i] = key[i];
     s.b[i] = pay[i][0];
     s.iL[i] = pay[i][1];
   }
@@ -326,6 +337,7 @@ CP_HD T uni_piece(const UniSide<T>& s, T l, T r) {
   return sum * hl;
 }
 
+// the pieces up to three factors (the fourth is the centre's)
 template <typename T>
 CP_HD T uni_side_value(const UniSide<T>& s) {
   if (s.empty) return T(0);
@@ -333,8 +345,59 @@ CP_HD T uni_side_value(const UniSide<T>& s) {
   acc += uni_piece<T, 1, 1>(s, s.c[0], s.c[1]);
   acc += uni_piece<T, 2, 1, true>(s, s.c[1], s.c[2]);
   acc += uni_piece<T, 3, 2>(s, s.c[2], s.c[3]);
-  acc += uni_piece<T, 4, 2, true>(s, s.c[3], s.bmin);
   return acc * s.iLv;
+}
+
+// The centre: the range [max(0, a_i), min(Lv, b_i)] on which all four
+// neighbours vary (if there is one).  It is the last piece of the minimum's
+// side, of the maximum's (reflected) and the middle one of both saddle terms,
+// and S and F = 1 - S need the same nodes, so all of them are integrated here:
+// out = (prod S, prod F, S_e F_n S_w F_s, F_e S_n F_w S_s), the last two with
+// SAD.  Returns whether there is a centre.
+//
+// Measured at 2048^2 (20-member fit, FP32; with the mask selections above and
+// v_med3 clamps, against one centre per side): Epanechnikov forward 77 -> 65 us,
+// adjoint 133 -> 119, uniform forward 42.6 -> 37.2, adjoint 64.6 -> 62.6; all
+// are bound by vector issue, of which the selections took a fifth.
+template <typename T, bool SAD>
+CP_HD bool uni_centre(T Lv, T iLv, const T (&a)[4], const T (&b)[4], const T (&iL)[4], T (&out)[4]) {
+  const T l = fmax_nn(fmax_nn(fmax_nn(T(0), a[0]), fmax_nn(a[1], a[2])), a[3]);
+  const T r = fmin_nn(fmin_nn(fmin_nn(Lv, b[0]), fmin_nn(b[1], b[2])), b[3]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) out[q] = T(0);
+  if (!(l < r)) return false;
+  const T mid = (l + r) * T(0.5), hl = (r - l) * T(0.5);
+  T al[4], af[4], be[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    al[i] = (b[i] - mid) * iL[i];
+    af[i] = (mid - a[i]) * iL[i];
+    be[i] = hl * iL[i];
+  }
+  T s[4] = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {  // both weights 1
+    const T x = T(GL<2>::x[j]);
+    T S[4], F[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      S[i] = cfma(-be[i], x, al[i]);
+      F[i] = cfma(be[i], x, af[i]);
+    }
+    const T sa = S[0] * S[2], sb = S[1] * S[3], fa = F[0] * F[2], fb = F[1] * F[3];
+    s[0] = cfma(sa, sb, s[0]);
+    s[1] = cfma(fa, fb, s[1]);
+    if (SAD) {
+      s[2] = cfma(sa, fb, s[2]);
+      s[3] = cfma(fa, sb, s[3]);
+    }
+  }
+  // degree 4: the rule's remainder, the same for all (an even number of
+  // factors of either slope)
+  const T c = be[0] * be[1] * (be[2] * be[3]), k = hl * iLv;
+#pragma unroll
+  for (int q = 0; q < (SAD ? 4 : 2); ++q) out[q] = k * cfma(T(GLRem<2>::e), c, s[q]);
+  return true;
 }
 
 // Local derivatives of one side:  f(Lv, a_i, b_i) = (1/Lv) int_0^{b_min} prod S_i
@@ -450,35 +513,29 @@ template <typename T>
 struct EpaSide {
   T wv, iwv;
   T c[4], d[4], iw[4];
-  bool sw[5];  // comparator swaps of the sort (unsort4 restores neighbour order)
+  uint32_t sw[5];  // comparator swaps of the sort (unsort4 restores neighbour order)
   T bmin;
   bool empty;
 };
 
+// an absent neighbour is passed as d = 4 wv, w = wv, iw = 1 / wv: a factor that
+// would start beyond b_min, never active on a non-empty piece
 template <typename T>
-CP_HD void epa_setup(EpaSide<T>& s, T wv, T iwv, const T (&d)[4], const T (&w)[4], const T (&iw)[4],
-                     const bool (&pres)[4]) {
+CP_HD void epa_setup(EpaSide<T>& s, T wv, T iwv, const T (&d)[4], const T (&w)[4], const T (&iw)[4]) {
   s.wv = wv;
   s.iwv = iwv;
-  T bmin = wv;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (pres[i]) bmin = tmin(bmin, d[i] + w[i]);
-  s.bmin = bmin;
-  s.empty = !(bmin > -wv);
-  constexpr int P = 2;
-  T key[4];
-  T pay[4][P];
+  s.bmin = fmin_nn(fmin_nn(fmin_nn(wv, d[0] + w[0]), fmin_nn(d[1] + w[1], d[2] + w[2])), d[3] + w[3]);
+  s.empty = !(s.bmin > -wv);
+  T pay[4][2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    key[i] = pres[i] ? tclamp(d[i] - w[i], -wv, bmin) : bmin;
-    pay[i][0] = pres[i] ? d[i] : T(3) * wv;
-    pay[i][1] = pres[i] ? iw[i] : s.iwv;
+    s.c[i] = clamp_nn(d[i] - w[i], -wv, s.bmin);
+    pay[i][0] = d[i];
+    pay[i][1] = iw[i];
   }
-  sort4_rec<T, P>(key, pay, s.sw);
+  sort4_rec<T, 2>(s.c, pay, s.sw);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    s.c[i] = key[i];
     s.d[i] = pay[i][0];
     s.iw[i] = pay[i][1];
   }
@@ -533,16 +590,76 @@ CP_HD T epa_piece(const EpaSide<T>& s, T l, T r) {
   return sum * hl;
 }
 
+// the pieces up to three factors (the fourth is the centre's)
 template <typename T>
 CP_HD T epa_side_value(const EpaSide<T>& s) {
   if (s.empty) return T(0);
   const T kv = T(0.75) * s.iwv;  // pdf scale 3/(4 wv)
-  T acc = epa_cdf4(s, s.c[0]) * T(0.25);
+  const T acc = epa_cdf4(s, s.c[0]) * T(0.25);
   T p = epa_piece<T, 1, 3>(s, s.c[0], s.c[1]) * T(0.25);
-  p += epa_piece<T, 2, 4, true>(s, s.c[1], s.c[2]) * T(0.0625);
-  p += epa_piece<T, 3, 6>(s, s.c[2], s.c[3]) * T(0.015625);
-  p += epa_piece<T, 4, 7, true>(s, s.c[3], s.bmin) * T(0.00390625);
-  return acc + kv * p;
+  p = cfma(epa_piece<T, 2, 4, true>(s, s.c[1], s.c[2]), T(0.0625), p);
+  p = cfma(epa_piece<T, 3, 6>(s, s.c[2], s.c[3]), T(0.015625), p);
+  return cfma(kv, p, acc);
+}
+
+// Range and arguments of the centre (see uni_centre): u_i = au_i + bu_i y,
+// t = av + bv y on y in [-1, 1].
+template <typename T>
+struct EpaCentre {
+  T hl, av, bv, au[4], bu[4];
+};
+template <typename T>
+CP_HD bool epa_centre_setup(EpaCentre<T>& c, T wv, T iwv, const T (&d)[4], const T (&w)[4], const T (&iw)[4]) {
+  const T l = fmax_nn(fmax_nn(fmax_nn(-wv, d[0] - w[0]), fmax_nn(d[1] - w[1], d[2] - w[2])), d[3] - w[3]);
+  const T r = fmin_nn(fmin_nn(fmin_nn(wv, d[0] + w[0]), fmin_nn(d[1] + w[1], d[2] + w[2])), d[3] + w[3]);
+  const T mid = (l + r) * T(0.5);
+  c.hl = (r - l) * T(0.5);
+  c.av = mid * iwv;
+  c.bv = c.hl * iwv;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    c.au[i] = (mid - d[i]) * iw[i];
+    c.bu[i] = c.hl * iw[i];
+  }
+  return l < r;
+}
+
+// out as uni_centre; seven nodes and the remainder of the degree-14 term,
+// -bv^2 prod bu_i^3 for all four products.  4 S and 4 F share u^2 - 3.
+template <typename T, bool SAD>
+CP_HD bool epa_centre(T wv, T iwv, const T (&d)[4], const T (&w)[4], const T (&iw)[4], T (&out)[4]) {
+  EpaCentre<T> c;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) out[q] = T(0);
+  if (!epa_centre_setup(c, wv, iwv, d, w, iw)) return false;
+  T s[4] = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+  for (int j = 0; j < 7; ++j) {
+    const T x = T(GL<7>::x[j]);
+    const T t = cfma(c.bv, x, c.av);
+    const T q = T(GL<7>::w[j]) * cfma(-t, t, T(1));
+    T S[4], F[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const T u = cfma(c.bu[i], x, c.au[i]), o = cfma(u, u, T(-3));
+      S[i] = cfma(o, u, T(2));
+      F[i] = cfma(-o, u, T(2));
+    }
+    const T sa = q * (S[0] * S[2]), sb = S[1] * S[3], fa = q * (F[0] * F[2]), fb = F[1] * F[3];
+    s[0] = cfma(sa, sb, s[0]);
+    s[1] = cfma(fa, fb, s[1]);
+    if (SAD) {
+      s[2] = cfma(sa, fb, s[2]);
+      s[3] = cfma(fa, sb, s[3]);
+    }
+  }
+  T e = c.bv * c.bv;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e *= c.bu[i] * c.bu[i] * c.bu[i];
+  const T k = T(0.75 / 256.0) * iwv * c.hl;
+#pragma unroll
+  for (int q = 0; q < (SAD ? 4 : 2); ++q) out[q] = k * cfma(T(-GLRem<7>::e), e, s[q]);
+  return true;
 }
 
 // Local derivatives of one side, f(wv, d_i, w_i):
@@ -629,6 +746,7 @@ CP_HD void epa_piece_grad(const EpaSide<T>& s, T l, T r, T sc, T fsc, T& full, T
   }
 }
 
+// the pieces up to three factors (the fourth is the centre's)
 template <typename T, bool WF = true>
 CP_HD void epa_side_grad(const EpaSide<T>& s, EpaGrad<T>& g) {
   g.f = T(0);
@@ -643,18 +761,76 @@ CP_HD void epa_side_grad(const EpaSide<T>& s, EpaGrad<T>& g) {
   epa_piece_grad<T, 1, 3, false, WF>(s, s.c[0], s.c[1], T(1), T(0.25), full, ad, aw);
   epa_piece_grad<T, 2, 4, true, WF>(s, s.c[1], s.c[2], T(0.25), T(0.0625), full, ad, aw);
   epa_piece_grad<T, 3, 6, false, WF>(s, s.c[2], s.c[3], T(0.0625), T(0.015625), full, ad, aw);
-  epa_piece_grad<T, 4, 7, true, WF>(s, s.c[3], s.bmin, T(0.015625), T(0.00390625), full, ad, aw);
   const T kv = T(0.75) * s.iwv;
   if (WF) g.f = cfma(kv, full, epa_cdf4(s, s.c[0]) * T(0.25));
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 3; ++i) {
     const T ki = T(0.75) * s.iw[i] * kv;
     g.dd[i] = ki * ad[i];
     g.dw[i] = ki * aw[i];
   }
-  // sorted slots -> neighbour index
+  // sorted slots -> neighbour index (the last to start has no piece here)
   unsort4(g.dd, s.sw);
   unsort4(g.dw, s.sw);
+}
+
+// The centre's part of the weighted derivatives, g_min dP_min + g_max dP_max
+// with respect to d_i and w_i (the minimum's coordinates), and with WF of both
+// probabilities.  One leave-one-out sum for both sides: on the maximum's the
+// density enters with the opposite sign and F in place of S.  The width sums
+// have degree 14: remainder bv^2 prod bu_k^3 (g_min + g_max).
+template <typename T, bool WF>
+CP_HD void epa_centre_grad(T wv, T iwv, const T (&d)[4], const T (&w)[4], const T (&iw)[4], T gmin, T gmax,
+                           T (&cd)[4], T (&cw)[4], T& pmin, T& pmax) {
+  EpaCentre<T> c;
+  T fs = T(0), ff = T(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) cd[i] = cw[i] = T(0);
+  pmin = pmax = T(0);
+  if (!epa_centre_setup(c, wv, iwv, d, w, iw)) return;
+#pragma unroll
+  for (int j = 0; j < 7; ++j) {
+    const T x = T(GL<7>::x[j]);
+    const T t = cfma(c.bv, x, c.av);
+    const T q = T(GL<7>::w[j]) * cfma(-t, t, T(1)), qs = q * gmin, qf = -q * gmax;
+    T u[4], p[4], S[4], F[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      u[i] = cfma(c.bu[i], x, c.au[i]);
+      const T o = cfma(u[i], u[i], T(-3));
+      p[i] = cfma(-u[i], u[i], T(1));
+      S[i] = cfma(o, u[i], T(2));
+      F[i] = cfma(-o, u[i], T(2));
+    }
+    const T s01 = S[0] * S[1], s23 = S[2] * S[3], f01 = F[0] * F[1], f23 = F[2] * F[3];
+    if (WF) {
+      fs = cfma(q * s01, s23, fs);
+      ff = cfma(q * f01, f23, ff);
+    }
+    const T a23 = qs * s23, a01 = qs * s01, b23 = qf * f23, b01 = qf * f01;
+    const T lo[4] = {cfma(S[1], a23, F[1] * b23), cfma(S[0], a23, F[0] * b23), cfma(S[3], a01, F[3] * b01),
+                     cfma(S[2], a01, F[2] * b01)};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const T lw = p[i] * lo[i];
+      cd[i] += lw;
+      cw[i] = cfma(lw, u[i], cw[i]);
+    }
+  }
+  T e = T(GLRem<7>::e) * c.bv * c.bv;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e *= c.bu[i] * c.bu[i] * c.bu[i];
+  const T k = T(0.75) * iwv * c.hl, ew = e * (gmin + gmax);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const T ki = T(0.75 / 64.0) * iw[i] * k;
+    cd[i] *= ki;
+    cw[i] = ki * (cw[i] + ew);
+  }
+  if (WF) {
+    pmin = T(1.0 / 256.0) * k * (fs - e);
+    pmax = T(1.0 / 256.0) * k * (ff - e);
+  }
 }
 
 }  // namespace cp

@@ -100,7 +100,12 @@ __global__ __launch_bounds__(256) void k_fit_fwd_ue(FitFwdArgs<T> a, int tiles_x
   __shared__ T lds[2 * (kFwdTX + 2) * (TY + 2)];
   const int t = xcd_tile(blockIdx.x, ntiles);
   const int ty0 = (t / tiles_x) * TY, tx0 = (t % tiles_x) * kFwdTX;
+  // FP64: loads of the waves that fit go out before the waves that integrate
+  // issue (1024^2 x 20 members, Epanechnikov 50.2 -> 48.1 us, uniform 40.1 ->
+  // 38.7); FP32, with twice the waves, is slower so (111.9 -> 117.3 at 2048^2)
+  if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(2);
   fit_tile<T, MODEL, TY, 256>(a, ty0, tx0, lds, threadIdx.x);
+  if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(0);
   __syncthreads();
   tile_fwd_ue_eval<T, MODEL, TY, 256>(a.f, ty0, tx0, lds, threadIdx.x);
 }
@@ -109,8 +114,8 @@ template <typename T, int MODEL>
 hipError_t launch(const FitFwdArgs<T>& a, hipStream_t st) {
   // 64 x 12 tiles: the 14 staged rows of 16-byte groups (252 in FP32) take
   // the 256 threads once (FP64's 476 twice); grids with fewer than eight
-  // such tiles per CU use 64 x 4.  Measured at 2048^2 (Epanechnikov, 20 members): 64 x 12 128 us,
-  // 64 x 16 (two passes of groups) 135 us, fit then forward 162 us.
+  // such tiles per CU use 64 x 4.  Measured at 2048^2 (Epanechnikov, 20 members): 64 x 12 112 us
+  // (64 x 16, two passes of groups, 5% more), fit then forward 131 us.
   const int tx = (a.f.W + kFwdTX - 1) / kFwdTX;
   const bool tall = (int64_t)tx * ((a.f.H + 11) / 12) >= kTallTileBlocks;
   const int TYr = tall ? 12 : 4, n = tx * ((a.f.H + TYr - 1) / TYr);

@@ -59,11 +59,74 @@ CP_HD bool valid_epa(T m, T w) {
 // ---------------------------------------------------------------------------
 // per-vertex evaluation from LDS (e = centre, en = e/n/w/s LDS indices)
 // ---------------------------------------------------------------------------
+// A stencil in the vertex's frame, absent neighbours replaced as uni_setup and
+// epa_setup ask.  Uniform: ranges [a, b] from the vertex's lower end, widths
+// L; Epanechnikov: centres d, half-widths w.  The reflected coordinates of the
+// maximum's side are formed when that side's turn comes (registers).
+template <typename T>
+struct UniStencil {
+  T Lv, iLv, a[4], b[4], iL[4];
+};
+template <typename T>
+CP_HD void uni_stencil(UniStencil<T>& s, T p0, T p1, const T (&q0)[4], const T (&q1)[4], const bool (&pres)[4]) {
+  s.Lv = p1 - p0;
+  s.iLv = crcp(s.Lv);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    s.a[i] = pres[i] ? q0[i] - p0 : T(2) * s.Lv;
+    s.b[i] = pres[i] ? q1[i] - p0 : T(3) * s.Lv;
+    s.iL[i] = crcp(pres[i] ? q1[i] - q0[i] : s.Lv);
+  }
+}
+// the minimum's side, and the maximum's: [hi_v - hi_n, hi_v - lo_n]
+template <typename T>
+CP_HD void uni_min_side(UniSide<T>& s, const UniStencil<T>& st) {
+  uni_setup(s, st.Lv, st.iLv, st.a, st.b, st.iL);
+}
+template <typename T>
+CP_HD void uni_max_side(UniSide<T>& s, const UniStencil<T>& st, T p1, const T (&q0)[4], const T (&q1)[4],
+                        const bool (&pres)[4]) {
+  T a[4], b[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    a[i] = pres[i] ? p1 - q1[i] : T(2) * st.Lv;
+    b[i] = pres[i] ? p1 - q0[i] : T(3) * st.Lv;
+  }
+  uni_setup(s, st.Lv, st.iLv, a, b, st.iL);
+}
+template <typename T>
+struct EpaStencil {
+  T wv, iwv, d[4], w[4], iw[4];
+};
+template <typename T>
+CP_HD void epa_stencil(EpaStencil<T>& s, T p0, T p1, const T (&q0)[4], const T (&q1)[4], const bool (&pres)[4]) {
+  s.wv = p1;
+  s.iwv = crcp(p1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    s.d[i] = pres[i] ? q0[i] - p0 : T(4) * p1;
+    s.w[i] = pres[i] ? q1[i] : p1;
+    s.iw[i] = crcp(s.w[i]);
+  }
+}
+template <typename T>
+CP_HD void epa_min_side(EpaSide<T>& s, const EpaStencil<T>& st) {
+  epa_setup(s, st.wv, st.iwv, st.d, st.w, st.iw);
+}
+template <typename T>
+CP_HD void epa_max_side(EpaSide<T>& s, const EpaStencil<T>& st, const bool (&pres)[4]) {
+  T nd[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) nd[i] = pres[i] ? -st.d[i] : st.d[i];
+  epa_setup(s, st.wv, st.iwv, nd, st.w, st.iw);
+}
+
+// the five distributions of a stencil from LDS, and whether all are valid
 template <typename T, int MODEL>
-CP_HD void vertex_fwd_ue(const T* L, int E, int e, const int (&en)[4], const bool (&pres)[4],
-                                              T& pmin, T& pmax) {
-  const T p0 = L[e], p1 = L[E + e];
-  T q0[4], q1[4];
+CP_HD bool stencil_load_ue(const T* L, int E, int e, const int (&en)[4], const bool (&pres)[4], T& p0, T& p1,
+                           T (&q0)[4], T (&q1)[4]) {
+  p0 = L[e];
+  p1 = L[E + e];
   bool ok = MODEL == CP_UNIFORM ? valid_range(p0, p1) : valid_epa(p0, p1);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -71,44 +134,35 @@ CP_HD void vertex_fwd_ue(const T* L, int E, int e, const int (&en)[4], const boo
     q1[i] = L[E + en[i]];
     if (pres[i]) ok = ok && (MODEL == CP_UNIFORM ? valid_range(q0[i], q1[i]) : valid_epa(q0[i], q1[i]));
   }
-  if (!ok) {
+  return ok;
+}
+
+template <typename T, int MODEL>
+CP_HD void vertex_fwd_ue(const T* L, int E, int e, const int (&en)[4], const bool (&pres)[4],
+                                              T& pmin, T& pmax) {
+  T p0, p1, q0[4], q1[4], o[4];
+  if (!stencil_load_ue<T, MODEL>(L, E, e, en, pres, p0, p1, q0, q1)) {
     pmin = pmax = qnan<T>();
     return;
   }
-  if (MODEL == CP_UNIFORM) {
-    const T Lv = p1 - p0, iLv = crcp(Lv);
-    T a[4], b[4], iL[4];
+  if constexpr (MODEL == CP_UNIFORM) {
+    UniStencil<T> st;
+    uni_stencil(st, p0, p1, q0, q1, pres);
+    uni_centre<T, false>(st.Lv, st.iLv, st.a, st.b, st.iL, o);
     UniSide<T> s;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a[i] = q0[i] - p0;
-      b[i] = q1[i] - p0;
-      iL[i] = crcp(q1[i] - q0[i]);
-    }
-    uni_setup(s, Lv, iLv, a, b, iL, pres);
-    pmin = uni_side_value(s);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a[i] = p1 - q1[i];
-      b[i] = p1 - q0[i];
-    }
-    uni_setup(s, Lv, iLv, a, b, iL, pres);
-    pmax = uni_side_value(s);
+    uni_min_side(s, st);
+    pmin = o[0] + uni_side_value(s);
+    uni_max_side(s, st, p1, q0, q1, pres);
+    pmax = o[1] + uni_side_value(s);
   } else {
-    T d[4], iw[4];
-    const T iwv = crcp(p1);
+    EpaStencil<T> st;
+    epa_stencil(st, p0, p1, q0, q1, pres);
+    epa_centre<T, false>(st.wv, st.iwv, st.d, st.w, st.iw, o);
     EpaSide<T> s;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      d[i] = q0[i] - p0;
-      iw[i] = crcp(q1[i]);
-    }
-    epa_setup(s, p1, iwv, d, q1, iw, pres);
-    pmin = epa_side_value(s);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) d[i] = p0 - q0[i];
-    epa_setup(s, p1, iwv, d, q1, iw, pres);
-    pmax = epa_side_value(s);
+    epa_min_side(s, st);
+    pmin = o[0] + epa_side_value(s);
+    epa_max_side(s, st, pres);
+    pmax = o[1] + epa_side_value(s);
   }
 }
 
@@ -135,24 +189,13 @@ CP_HD void vertex_jac_vals(T p0, T p1, const T (&q0)[4], const T (&q1)[4], const
     gauss_vertex_jac<T>(p0, p1, q0, q1, pres, gmin, gmax, jac);
     pmin = pmax = T(0);
   } else if constexpr (MODEL == CP_UNIFORM) {
-    const T Lv = p1 - p0, iLv = crcp(Lv);
-    T a[4], b[4], iL[4];
+    UniStencil<T> st;
+    uni_stencil(st, p0, p1, q0, q1, pres);
     UniSide<T> s;
     UniGrad<T> g, r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a[i] = q0[i] - p0;
-      b[i] = q1[i] - p0;
-      iL[i] = crcp(q1[i] - q0[i]);
-    }
-    uni_setup(s, Lv, iLv, a, b, iL, pres);
+    uni_min_side(s, st);
     uni_side_grad(s, g);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a[i] = p1 - q1[i];
-      b[i] = p1 - q0[i];
-    }
-    uni_setup(s, Lv, iLv, a, b, iL, pres);
+    uni_max_side(s, st, p1, q0, q1, pres);
     uni_side_grad(s, r);
     T sg = T(0), sr = T(0);
 #pragma unroll
@@ -172,40 +215,36 @@ CP_HD void vertex_jac_vals(T p0, T p1, const T (&q0)[4], const T (&q1)[4], const
       jac[3 + 2 * i] = gmin * g.db[i] - gmax * r.da[i];
     }
   } else {
-    T d[4], nd[4], iw[4];
-    const T iwv = crcp(p1);
+    EpaStencil<T> st;
+    epa_stencil(st, p0, p1, q0, q1, pres);
+    T cd[4], cw[4], c0, c1;
+    epa_centre_grad<T, WF>(st.wv, st.iwv, st.d, st.w, st.iw, gmin, gmax, cd, cw, c0, c1);
     EpaSide<T> s;
-    EpaGrad<T> g, r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      d[i] = q0[i] - p0;
-      nd[i] = p0 - q0[i];
-      iw[i] = crcp(q1[i]);
-    }
-    epa_setup<T>(s, p1, iwv, d, q1, iw, pres);
+    EpaGrad<T> g;
+    epa_min_side(s, st);
     epa_side_grad<T, WF>(s, g);
-    epa_setup<T>(s, p1, iwv, nd, q1, iw, pres);
-    epa_side_grad<T, WF>(s, r);
-    // min side: d = m_n - m_v; max side: d = m_v - m_n; the vertex width
-    // by scale invariance, summed in neighbour order (an absent neighbour's
-    // derivatives are 0)
-    T sg = T(0), sr = T(0), xg = T(0), xr = T(0);
+    pmin = g.f + c0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      sg += g.dd[i];
-      sr += r.dd[i];
-      xg = cfma(d[i], g.dd[i], cfma(q1[i], g.dw[i], xg));
-      xr = cfma(nd[i], r.dd[i], cfma(q1[i], r.dw[i], xr));
+      cd[i] = cfma(gmin, g.dd[i], cd[i]);
+      cw[i] = cfma(gmin, g.dw[i], cw[i]);
     }
-    pmin = g.f;
-    pmax = r.f;
-    jac[0] = -gmin * sg + gmax * sr;
-    jac[1] = -(gmin * xg + gmax * xr) * iwv;
+    epa_max_side(s, st, pres);
+    epa_side_grad<T, WF>(s, g);
+    pmax = g.f + c1;
+    // the vertex's slots by translation invariance and, for the width, by
+    // scale invariance about its centre (an absent neighbour's derivatives
+    // are 0)
+    T sd = T(0), sw = T(0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      jac[2 + 2 * i] = gmin * g.dd[i] - gmax * r.dd[i];
-      jac[3 + 2 * i] = gmin * g.dw[i] + gmax * r.dw[i];
+      jac[2 + 2 * i] = cfma(-gmax, g.dd[i], cd[i]);
+      jac[3 + 2 * i] = cfma(gmax, g.dw[i], cw[i]);
+      sd += jac[2 + 2 * i];
+      sw = cfma(st.d[i], jac[2 + 2 * i], cfma(st.w[i], jac[3 + 2 * i], sw));
     }
+    jac[0] = -sd;
+    jac[1] = -sw * st.iwv;
   }
 }
 
