@@ -7,6 +7,7 @@ have a row stride larger than W (all planes of one call must share it).
 """
 from __future__ import annotations
 
+import functools
 from dataclasses import dataclass
 
 import torch
@@ -15,14 +16,20 @@ from . import _lib as L
 
 MODELS = {"uniform": L.CP_UNIFORM, "epanechnikov": L.CP_EPANECHNIKOV, "histogram": L.CP_HISTOGRAM,
           "mvg": L.CP_MVGAUSS, "gaussian": L.CP_GAUSSIAN}
+_DTYPES = {torch.float32: L.CP_F32, torch.float64: L.CP_F64}
 
 
 def model_id(model) -> int:
     return MODELS[model] if isinstance(model, str) else int(model)
 
 
+@functools.lru_cache(maxsize=256, typed=True)
+def _n_params(model: int, nbins: int) -> int:
+    return L.cp_n_params(model, nbins)
+
+
 def n_params(model, nbins: int = 0) -> int:
-    n = L.cp_n_params(model_id(model), nbins)
+    n = _n_params(model_id(model), nbins)
     if n < 0:
         raise ValueError("unknown model or bad nbins")
     return n
@@ -43,7 +50,7 @@ class Field:
     row_stride: int = 0
 
     def desc(self) -> L.cp_field_desc_t:
-        dt = {torch.float32: L.CP_F32, torch.float64: L.CP_F64}[self.dtype]
+        dt = _DTYPES[self.dtype]
         return L.cp_field_desc_t(self.height, self.width, self.row_stride, model_id(self.model), dt, self.nbins,
                                  self.nsamples, self.seed, self.field_id, self.estimator)
 
@@ -60,15 +67,22 @@ class Field:
         return torch.float32 if model_id(self.model) == L.CP_MVGAUSS else self.dtype
 
 
+# A call's host part is some microseconds, as long as a small field's kernels
+# take, so the checks below look at each attribute once and fall through to the
+# general form only to say what is wrong.  (A 64 x 64 forward: 15.7 -> 9.5 us of
+# host time; error-bound fit and classification 29.9 -> 22.8.)
+
+
 def _stream(t: torch.Tensor) -> int:
     """The current stream of t's device; the library works on the current
     HIP device, so t must live there."""
-    if t.device.type != "cuda":
+    i = t.get_device()
+    if i < 0 or not t.is_cuda:
         raise ValueError(f"expected a GPU tensor, got one on {t.device}")
-    if t.device.index != torch.cuda.current_device():
+    if i != torch._C._cuda_getDevice():
         raise ValueError(f"tensors on {t.device} but the current device is cuda:{torch.cuda.current_device()}: "
                          "call under torch.cuda.device(...)")
-    return torch.cuda.current_stream(t.device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(i)
 
 
 def _ptr(t: torch.Tensor | None):
@@ -76,6 +90,14 @@ def _ptr(t: torch.Tensor | None):
 
 
 def _planes(t: torch.Tensor, H: int, W: int, dtype: torch.dtype, name: str, row_stride: int = 0) -> None:
+    rs = row_stride or W
+    if t.is_cuda and t.dtype is dtype:
+        sh, st = t.shape, t.stride()
+        if len(st) == 3:
+            if sh[1] == H and sh[2] == W and st[2] == 1 and st[1] == rs and (sh[0] <= 1 or st[0] == H * rs):
+                return
+        elif len(st) == 2 and sh[0] == H and sh[1] == W and st[1] == 1 and st[0] == rs:
+            return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.dtype != dtype:
@@ -84,9 +106,19 @@ def _planes(t: torch.Tensor, H: int, W: int, dtype: torch.dtype, name: str, row_
         t = t.unsqueeze(0)
     if t.dim() != 3 or t.shape[1] != H or t.shape[2] != W:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected [*, {H}, {W}]")
-    rs = row_stride or W
-    if t.stride(2) != 1 or t.stride(1) != rs or (t.shape[0] > 1 and t.stride(0) != H * rs):
-        raise ValueError(f"{name} must be dense planes with row stride {rs}")
+    raise ValueError(f"{name} must be dense planes with row stride {rs}")
+
+
+def _output(t: torch.Tensor | None, H: int, W: int, dtype: torch.dtype, name: str, like: torch.Tensor,
+            row_stride: int = 0) -> torch.Tensor:
+    """The caller's output plane, checked, or a new one on like's device (dense:
+    checked only where the call asks for another row stride)."""
+    if t is None:
+        t = torch.empty((H, W), dtype=dtype, device=like.device)
+        if row_stride == 0 or row_stride == W:
+            return t
+    _planes(t, H, W, dtype, name, row_stride)
+    return t
 
 
 def field_of(params: torch.Tensor, model, nbins: int = 0, **kw) -> Field:
@@ -124,12 +156,9 @@ def fit_forward(members: torch.Tensor, model, nbins: int = 0, ddof: int = 1, bw_
     if out is None:
         out = torch.empty((f.n_param, H, W), dtype=f.param_dtype, device=members.device)
     _planes(out, H, W, f.param_dtype, "params")
-    if pmin is None:
-        pmin = torch.empty((H, W), dtype=f.out_dtype, device=members.device)
-    if pmax is None:
-        pmax = torch.empty((H, W), dtype=f.out_dtype, device=members.device)
-    _planes(pmin, H, W, f.out_dtype, "p_min")
-    _planes(pmax, H, W, f.out_dtype, "p_max")
+    od = f.out_dtype
+    pmin = _output(pmin, H, W, od, "p_min", members)
+    pmax = _output(pmax, H, W, od, "p_max", members)
     opts = L.cp_fit_opts_t(ddof, bw_factor, cov_jitter, degenerate_eps)
     L.check(L.cp_fit_forward(f.desc(), _ptr(members), M, opts, _ptr(out), _ptr(pmin), _ptr(pmax),
                              _stream(members)))
@@ -151,15 +180,12 @@ def fit_error_bound(decompressed: torch.Tensor, eb: float, out: torch.Tensor | N
 
 def forward(params: torch.Tensor, f: Field, pmin: torch.Tensor | None = None, pmax: torch.Tensor | None = None):
     """cp_prob_forward: (P_min, P_max) of every vertex."""
-    _planes(params, f.height, f.width, f.param_dtype, "params", f.row_stride)
+    H, W, rs, od = f.height, f.width, f.row_stride, f.out_dtype
+    _planes(params, H, W, f.param_dtype, "params", rs)
     if params.shape[0] != f.n_param:
         raise ValueError(f"params needs {f.n_param} planes")
-    if pmin is None:
-        pmin = torch.empty((f.height, f.width), dtype=f.out_dtype, device=params.device)
-    if pmax is None:
-        pmax = torch.empty((f.height, f.width), dtype=f.out_dtype, device=params.device)
-    _planes(pmin, f.height, f.width, f.out_dtype, "p_min", f.row_stride)
-    _planes(pmax, f.height, f.width, f.out_dtype, "p_max", f.row_stride)
+    pmin = _output(pmin, H, W, od, "p_min", params, rs)
+    pmax = _output(pmax, H, W, od, "p_max", params, rs)
     L.check(L.cp_prob_forward(f.desc(), _ptr(params), _ptr(pmin), _ptr(pmax), _stream(params)))
     return pmin, pmax
 
@@ -169,12 +195,13 @@ def backward(params: torch.Tensor, gmin: torch.Tensor, gmax: torch.Tensor, f: Fi
     """cp_prob_backward: gradient of sum g_min P_min + g_max P_max w.r.t. params.
     noalloc=True calls cp_prob_backward_noalloc (the library's fixed scratch
     array instead of a workspace it allocates; pass `grad` to allocate nothing)."""
-    _planes(params, f.height, f.width, f.param_dtype, "params", f.row_stride)
-    _planes(gmin, f.height, f.width, f.out_dtype, "g_min", f.row_stride)
-    _planes(gmax, f.height, f.width, f.out_dtype, "g_max", f.row_stride)
+    H, W, rs, od, pd = f.height, f.width, f.row_stride, f.out_dtype, f.param_dtype
+    _planes(params, H, W, pd, "params", rs)
+    _planes(gmin, H, W, od, "g_min", rs)
+    _planes(gmax, H, W, od, "g_max", rs)
     if grad is None:
         grad = torch.empty_like(params)
-    _planes(grad, f.height, f.width, f.param_dtype, "grad_params", f.row_stride)
+    _planes(grad, H, W, pd, "grad_params", rs)
     fn = L.cp_prob_backward_noalloc if noalloc else L.cp_prob_backward
     L.check(fn(f.desc(), _ptr(params), _ptr(gmin), _ptr(gmax), _ptr(grad), _stream(params)))
     return grad
@@ -192,9 +219,10 @@ def classify(params: torch.Tensor, f: Field, outputs=("min", "max", "saddle", "r
     names = set(outputs)
     if not names <= {"min", "max", "saddle", "regular"}:
         raise ValueError(f"unknown outputs {sorted(names)}")
-    out = {k: torch.empty((f.height, f.width), dtype=f.out_dtype, device=params.device) for k in sorted(names)}
+    shape, od, dev = (f.height, f.width), f.out_dtype, params.device
+    out = {k: torch.empty(shape, dtype=od, device=dev) for k in sorted(names)}
     if terms:
-        out["terms"] = torch.empty((2, f.height, f.width), dtype=f.out_dtype, device=params.device)
+        out["terms"] = torch.empty((2, *shape), dtype=od, device=dev)
     L.check(L.cp_prob_classify(f.desc(), _ptr(params), _ptr(out.get("min")), _ptr(out.get("max")),
                                _ptr(out.get("saddle")), _ptr(out.get("regular")), _ptr(out.get("terms")),
                                _stream(params)))
