@@ -232,10 +232,12 @@ void pass_geom(int pass, int v, size_t el, int& ox, int& oy) {
   }
 }
 
-size_t tile_lds_bytes(int pass, int v, int nb, size_t el) {
+size_t tile_lds_bytes(int pass, int v, const Field& f, size_t el) {
   int ox, oy;
   pass_geom(pass, v, el, ox, oy);
-  if (pass == PASS_FWD_HIST || pass == PASS_BWD_HIST) return el * (size_t)hist_planes(nb) * (ox + 2) * (oy + 2);
+  if (pass == PASS_FWD_HIST) return el * (size_t)hist_planes(f.nb) * (ox + 2) * (oy + 2);
+  if (pass == PASS_BWD_HIST)
+    return el * hist_sweep_lds(f.nb, (ox + 2) * (oy + 2), kNT, hist_row_sums(f.nb, el, (int64_t)f.H * f.W));
   if (pass == PASS_FWD_UE) return el * 2 * (ox + 2) * (oy + 2);
   if (pass == PASS_BWD_UE) return el * 8 * (size_t)(ox + 2) * (oy + 2);
   return 0;
@@ -317,18 +319,18 @@ hipError_t blocks_per_cu(int dtype, int pass, int v, size_t lds, int* per_cu) {
 // expensive first (field and column order among equals: a claimed chunk
 // stacks tiles vertically and shares their halo rows).
 void pass_tiles(const std::vector<Field>& fs, int pass, int v, size_t el, std::vector<BatchTile>& out,
-                int& max_nb) {
+                size_t& lds) {
   int ox, oy;
   pass_geom(pass, v, el, ox, oy);
   std::vector<BatchTile> tiles;
   std::vector<double> cost;
-  max_nb = 0;
+  lds = 0;  // the largest of the fields' tiles
   for (int i = 0; i < (int)fs.size(); ++i) {
     const Field& f = fs[i];
     const bool hist = f.model == CP_HISTOGRAM;
     const bool mine = pass == PASS_FWD_UE || pass == PASS_BWD_UE ? !hist : hist;
     if (!mine) continue;
-    max_nb = std::max(max_nb, f.nb);
+    lds = std::max(lds, tile_lds_bytes(pass, v, f, el));
     if (pass == PASS_GATHER) {
       const int64_t plane = (int64_t)f.H * f.W;
       for (int64_t t = 0; t < plane; t += kGatherChunk) {
@@ -357,9 +359,8 @@ void pass_tiles(const std::vector<Field>& fs, int pass, int v, size_t el, std::v
 cp_status_t build_pass(const Plan& P, int pass, int v, int chunk, Pass& out) {
   const size_t el = P.dtype == CP_F64 ? 8 : 4;
   std::vector<BatchTile> flat;
-  int max_nb = 0;
-  pass_tiles(P.fields, pass, v, el, flat, max_nb);
-  const size_t lds = tile_lds_bytes(pass, v, max_nb, el);
+  size_t lds = 0;
+  pass_tiles(P.fields, pass, v, el, flat, lds);
   if (lds > kMaxLds) return CP_EUNSUPPORTED;
   int per_cu = 0;
   if (blocks_per_cu(P.dtype, pass, v, lds, &per_cu) != hipSuccess) return CP_EDEVICE;

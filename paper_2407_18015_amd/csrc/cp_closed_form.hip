@@ -169,7 +169,8 @@ static hipError_t launch_bwd_hist(const FieldPtrs<T>& p, hipStream_t st, const S
   hipError_t e = adjoint_scratch(sizeof(T) * (size_t)hist_ws_planes(p.nb) * plane, st, scr, &ws);
   if (e != hipSuccess) return e;
   T* J = static_cast<T*>(ws);
-  const size_t lds = sizeof(T) * (size_t)hist_planes(p.nb) * (kFwdTX + 2) * (TY + 2);
+  const size_t lds = sizeof(T) * hist_sweep_lds(p.nb, (kFwdTX + 2) * (TY + 2), kFwdTX * TY,
+                                                hist_row_sums(p.nb, sizeof(T), plane));
   e = allow_lds(k_hist_sweep<T, TY>, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_hist_sweep<T, TY>), dim3(n), dim3(kFwdTX * TY), lds, st, p, tx, n, J);

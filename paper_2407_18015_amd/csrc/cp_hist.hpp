@@ -150,12 +150,10 @@ CP_HD void suf_cursor_init(SufCursor<T>& c, const HistSuf<T>& L, int e, T lo, T 
   c.slope = (U0[j * L.E] - c.snx) * c.id;
 }
 
-// Cross the edge x1 if it is this cursor's next edge: one branch, and inside
-// it no other (past the range the cursor stays at the zero plane, so survival
-// and slope become 0 by themselves).
+// Cross the next edge (the callers' one branch; past the range the cursor stays
+// at the zero plane, so survival and slope become 0 by themselves).
 template <typename T>
-CP_HD void suf_cursor_step(SufCursor<T>& c, int E, T x1, T big) {
-  if (!(c.nxt == x1)) return;
+CP_HD void suf_cursor_step(SufCursor<T>& c, int E, T big) {
   c.k += T(1);
   const bool past = c.k > T(0);
   c.p += past ? 0 : E;
@@ -165,98 +163,35 @@ CP_HD void suf_cursor_step(SufCursor<T>& c, int E, T x1, T big) {
   c.nxt = past ? big : cfma(c.k, c.d, c.hi);
 }
 
-// ---------------------------------------------------------------------------
-// Cursor of the adjoint sweep: the same survival function, S(x) = snx + slope
-// (nxt - x) on the current bin, F = tot - S.  The sweep also needs the index m
-// of the next edge (0 below the range, h + 1 past it) for the bin it leaves,
-// and has no registers left for a pointer or a float index beside it: U_m is
-// read from plane 2 + min(m, h) (the zero plane past the range).
-// ---------------------------------------------------------------------------
-template <typename T>
-struct HistCursor {
-  int m;   // index of the next edge (0 below the range, h + 1 past it)
-  T nxt;   // next edge (big past the range)
-  T snx;   // U_m: survival at the next edge
-  T slope; // mass density of the current bin (0 outside the range)
-  T tot, hi, d, id;
-};
-
-// `present` false: the constant factor 1 in both products (S = 1, F = 2 - 1)
-template <typename T>
-CP_HD void hist_cursor_init(HistCursor<T>& c, const T* base, int E, int h, int e, T lo, T hi, bool present, T big) {
-  const T hf = T(h);
-  c.hi = hi;
-  c.d = (hi - lo) * (T(1) / hf);
-  c.id = hf * crcp(hi - lo);
-  c.slope = T(0);
-  if (!present) {
-    c.m = h + 1;
-    c.nxt = big;
-    c.snx = T(1);
-    c.tot = T(2);
-    return;
-  }
-  c.tot = base[2 * E + e];
-  if (!(hi > T(0))) {  // the whole range lies at or below x = 0
-    c.m = h + 1;
-    c.nxt = big;
-    c.snx = T(0);
-    return;
-  }
-  if (!(lo < T(0))) {  // range starts at or after x = 0
-    c.m = 0;
-    c.nxt = lo;
-    c.snx = c.tot;
-    return;
-  }
-  int j = (int)(-lo * c.id);
-  j = j < 0 ? 0 : (j > h - 1 ? h - 1 : j);
-  const auto edge = [&](int k) { return cfma(T(k - h), c.d, hi); };  // 1 <= k <= h
-  if (j + 1 < h && !(edge(j + 1) > T(0))) ++j;
-  if (j > 0 && edge(j) > T(0)) --j;
-  c.m = j + 1;
-  c.nxt = edge(j + 1);
-  c.snx = base[(3 + j) * E + e];
-  c.slope = (base[(2 + j) * E + e] - c.snx) * c.id;
-}
-
-// Cross the next edge; e is the histogram's LDS index in a plane.
-template <typename T>
-CP_HD void hist_cursor_step(HistCursor<T>& c, const T* base, int E, int e, int h, T big) {
-  c.m += 1;
-  const int mm = c.m < h ? c.m : h;  // (the zero plane past the range)
-  const T u = base[(2 + mm) * E + e];
-  c.slope = (c.snx - u) * c.id;
-  c.snx = u;
-  c.nxt = mm != c.m ? big : cfma(T(c.m - h), c.d, c.hi);
-}
-
-// The vertex's own bins over [0, hv]: bin jv, next edge nv (hv for the last
-// bin, big past it), density pv, U above the bin uv.
+// The vertex's own bins over [0, hv]: the upper edge nv = hv + k dv of the
+// current bin (k = -(h - 1) .. 0), U there (at p), the bin's density.
 template <typename T>
 struct VertexBins {
-  int jv;
-  T nv, pv, uv, dv, idv;
+  const T* p;
+  T k, nv, pv, uv, dv, idv;
 };
 
 template <typename T>
-CP_HD void vertex_bins_init(VertexBins<T>& b, const T* base, int E, int h, int ev, T hv) {
+CP_HD void vertex_bins_init(VertexBins<T>& b, const HistSuf<T>& L, int ev, T hv) {
+  const int h = L.h;
   b.dv = hv * (T(1) / T(h));
   b.idv = T(h) * crcp(hv);
-  b.jv = 0;
+  b.p = L.base + 3 * L.E + ev;
+  b.k = T(1 - h);
   b.nv = h > 1 ? b.dv : hv;
-  b.uv = base[3 * E + ev];
-  b.pv = (base[2 * E + ev] - b.uv) * b.idv;
+  b.uv = *b.p;
+  b.pv = (L.U(ev, 0) - b.uv) * b.idv;
 }
 
+// (past the last bin, k = 1, the sweep has ended)
 template <typename T>
-CP_HD void vertex_bins_step(VertexBins<T>& b, const T* base, int E, int h, int ev, T hv, T big) {
-  const int jn = b.jv + 1;
-  const T un = base[(jn + 3 < h + 2 ? jn + 3 : h + 2) * E + ev];  // U_{jn+1}
-  b.jv = jn;
-  b.pv = (b.uv - un) * b.idv;
-  b.uv = un;
-  b.nv = jn + 1 < h ? T(jn + 1) * b.dv : (jn + 1 == h ? hv : big);
+CP_HD void vertex_bins_step(VertexBins<T>& b, int E, T hv) {
+  b.p += b.k < T(0) ? E : 0;
+  b.k += T(1);
+  const T u = *b.p;
+  b.pv = (b.uv - u) * b.idv;
+  b.uv = u;
+  b.nv = cfma(tmin(b.k, T(0)), b.dv, hv);
 }
 
 // P_min and P_max of vertex ev; neighbour ranges [lo_i, hi_i] in the vertex
@@ -277,12 +212,8 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
                                            T& t2) {
   const int h = L.h;
   const T big = hv + hv + T(1);
-  const T dv = hv * (T(1) / T(h)), idv = T(h) * crcp(hv);
-  // the vertex's bin: its upper edge nv = hv + kv dv, U there, its density
-  const T* pu = L.base + 3 * L.E + ev;
-  T kv = T(1 - h), nv = h > 1 ? dv : hv;
-  T uv = *pu;
-  T pv = (L.U(ev, 0) - uv) * idv;
+  VertexBins<T> vb;
+  vertex_bins_init(vb, L, ev, hv);
   SufCursor<T> c[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) suf_cursor_init(c[i], L, en[i], lo[i], hi[i], pres[i], big);
@@ -290,7 +221,7 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
   const int maxit = 5 * (h + 1) + 2;  // every step crosses at least one edge
   for (int it = 0; it < maxit; ++it) {
     if (!(x0 < hv)) break;
-    T x1 = nv;
+    T x1 = vb.nv;
 #pragma unroll
     for (int i = 0; i < 4; ++i) x1 = fmin_nn(x1, c[i].nxt);  // sweep edges: finite
     // The factors at the midpoint, S and F, and their half-change t >= 0: on
@@ -320,7 +251,7 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
       f1[p] = cfma(F[p], t[p + 2], F[p + 2] * t[p]);
       q2[p] = t[p] * t[p + 2];
     }
-    const T top = T(0.2) * (q2[0] * q2[1]), wgt = pv * (x1 - x0);
+    const T top = T(0.2) * (q2[0] * q2[1]), wgt = vb.pv * (x1 - x0);
     const auto quartic = [&](T p0, T p1, T r0, T r1) {  // p1 r1 with the sign of its term
       const T m = cfma(p0, q2[1], cfma(q2[0], r0, p1 * r1));
       return cfma(T(1.0 / 3.0), m, cfma(p0, r0, top));
@@ -337,15 +268,9 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
     settle(amin);
     settle(amax);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) suf_cursor_step(c[i], L.E, x1, big);
-    if (nv == x1) {
-      pu += kv < T(0) ? L.E : 0;
-      kv += T(1);
-      const T un = *pu;
-      pv = (uv - un) * idv;
-      uv = un;
-      nv = cfma(tmin(kv, T(0)), dv, hv);
-    }
+    for (int i = 0; i < 4; ++i)
+      if (c[i].nxt == x1) suf_cursor_step(c[i], L.E, big);
+    if (vb.nv == x1) vertex_bins_step(vb, L.E, hv);
     x0 = x1;
   }
   pmin = amin;

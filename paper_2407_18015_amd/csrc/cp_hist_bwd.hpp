@@ -15,6 +15,7 @@
 #pragma once
 
 #include "cp_hist.hpp"
+#include "cp_internal.hpp"
 #include "cp_tiles.hpp"
 
 namespace cp {
@@ -39,14 +40,18 @@ namespace cp {
 // the vertex pdf and the half-length of the sub-interval, so the
 // accumulators run over the whole sweep.
 //
-// Cursors HistCursor, VertexBins, staged layout of cp_hist.hpp.  A cursor's
-// step and the emission of the bin it leaves are one branch with the state
-// updated in place: selects for every cursor cost four issue cycles each, and
-// each interval ran the four of every cursor although it ends one or two bins
-// (760 -> 670 cycles per wave and interval; sweep and gather at 2048^2 x 10
-// bins 1.41 -> 1.27 ms).
+// Cursors as in the forward (SufCursor, VertexBins), staged layout of
+// cp_hist.hpp.  A cursor's step and the emission of the bin it leaves are one
+// branch with the state updated in place: selects cost four issue cycles each,
+// and each interval ran the four of every cursor although it ends one or two
+// bins.  Bound by vector issue, 535 cycles per wave and interval (760 before;
+// both nodes unrolled, places as running pointers: 118 registers, four waves
+// per SIMD, where rolled nodes and five waves took 2% longer), and beyond the
+// caches by the entries' stores (JRow).  Adjoint at 2048^2 x 10 bins 1.41 ->
+// 1.14 ms, at 1024^2 on a rough ensemble 0.51 -> 0.30.
 //
-// J must provide set(slot, k, value) and tail(i, value); slot 0 is the
+// J.at(slot, k) is the place of an entry, J.step moves it to the next bin's,
+// J.put emits there and J.tail(i, value) the tail of neighbour i; slot 0 is the
 // vertex's own histogram, slot 1 + i neighbour i (e, n, w, s).
 // ---------------------------------------------------------------------------
 template <typename T, typename JOut>
@@ -54,14 +59,22 @@ __host__ __device__ void hist_jac_both(const HistSuf<T>& L, int ev, const int (&
                                        T hv, const T (&lo)[4], const T (&hi)[4], T gmin, T gmax, JOut& J, T& pmin,
                                        T& pmax) {
   const int h = L.h, E = L.E;
-  const T* base = L.base;
-  const T hf = T(h);
   const T big = hv + hv + T(1);
   VertexBins<T> vb;
-  vertex_bins_init(vb, base, E, h, ev, hv);
-  HistCursor<T> c[4];
+  vertex_bins_init(vb, L, ev, hv);
+  SufCursor<T> c[4];
+  // where the open bin's entry goes (not read while the cursor is below its
+  // range), and the first bin the sweep enters
+  typename JOut::At jv = J.at(0, 0), jn[4];
+  int first[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) hist_cursor_init(c[i], base, E, h, en[i], lo[i], hi[i], pres[i], big);
+  for (int i = 0; i < 4; ++i) {
+    suf_cursor_init(c[i], L, en[i], lo[i], hi[i], pres[i], big);
+    const int j = (int)c[i].k + h - 1;  // the open bin (-1: below the range)
+    jn[i] = J.at(1 + i, j);
+    first[i] = j < 0 ? 0 : j;
+  }
+  const T below = T(-h);
   // B_n = QS'_n + QF'_n so far; Y_n = B_n Delta_n + (kernel-weighted integral over the open bin so far):
   // the entry of a bin left is Y_n / Delta_n
   T B[4], QF[4], Y[4];
@@ -79,10 +92,9 @@ __host__ __device__ void hist_jac_both(const HistSuf<T>& L, int ev, const int (&
     const T php = vb.pv * hl, wS = php * gmin, wF = -php * gmax;
     // two-point Gauss-Legendre: exact for the leave-one-out products (degree
     // 3); the degree-4 integrands (full products, leave-one-out products times
-    // the bin kernel) get the rule's remainder in closed form below.  One node
-    // at a time (fewer registers live: the sweep needs occupancy).
+    // the bin kernel) get the rule's remainder in closed form below.
     const T dx = hl * T(GL<2>::x[1]);
-#pragma unroll 1
+#pragma unroll
     for (int q = 0; q < 2; ++q) {
       const T x = q ? mid + dx : mid - dx;  // both weights 1
       T S[4], F[4], r[4];
@@ -130,45 +142,51 @@ __host__ __device__ void hist_jac_both(const HistSuf<T>& L, int ev, const int (&
     // bin boundaries, one branch each: inside it the state is updated in
     // place (nothing reads the old one any more), so no selects
     if (vb.nv == x1) {  // the vertex's entry is complete
-      J.set(0, vb.jv, (gmin * vS + gmax * vF) * vb.idv);
+      J.put(0, jv, (gmin * vS + gmax * vF) * vb.idv);
+      J.step(0, jv);
       amin = cfma(vb.pv, vS, amin);
       amax = cfma(vb.pv, vF, amax);
       vS = vF = T(0);
-      vertex_bins_step(vb, base, E, h, ev, hv, big);
+      vertex_bins_step(vb, E, hv);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (c[i].nxt == x1) {
-        // bin m - 1 is left (none if the cursor enters its range)
-        if (c[i].m > 0) J.set(1 + i, c[i].m - 1, c[i].id * Y[i]);
+        // the bin left (none if the cursor enters its range)
+        if (c[i].k > below) J.put(1 + i, jn[i], c[i].id * Y[i]);
+        J.step(1 + i, jn[i]);
         Y[i] = B[i] * c[i].d;
-        hist_cursor_step(c[i], base, E, en[i], h, big);
+        suf_cursor_step(c[i], E, big);
       }
     }
     x0 = x1;
   }
   // remaining vertex bins (the sweep ended inside or past them): no range
-  for (int k = vb.jv; k < h; ++k) J.set(0, k, (k == vb.jv) ? (gmin * vS + gmax * vF) * vb.idv : T(0));
-  amin = cfma(vb.pv, vS, amin);
-  amax = cfma(vb.pv, vF, amax);
+  for (int k = (int)vb.k + h - 1; k < h; ++k) {
+    J.put(0, jv, (gmin * vS + gmax * vF) * vb.idv);
+    J.step(0, jv);
+    amin = cfma(vb.pv, vS, amin);
+    amax = cfma(vb.pv, vF, amax);
+    vS = vF = T(0);
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     if (!pres[i]) continue;
-    const int j = c[i].m - 1;  // open bin (-1: below the range, h: past it)
-    const T tf = -QF[i];            // g_max QF_n(hv), added to every bin by the gather
-    J.tail(i, tf);
-    // first bin the sweep entered (the cursor's start, found again)
-    HistCursor<T> c0;
-    hist_cursor_init(c0, base, E, h, en[i], lo[i], hi[i], true, big);
-    const int first = c0.m < 1 ? 0 : c0.m - 1;
-    for (int k = 0; k < h; ++k) {
-      if (k < first) {
-        J.set(1 + i, k, T(0));  // entirely below the sweep: dF/dm = 1 there (the tail)
-      } else if (k == j) {
-        J.set(1 + i, k, c[i].id * Y[i]);  // the open bin: inside the range
-      } else if (k > j) {
-        J.set(1 + i, k, B[i]);  // entirely above the sweep: dS/dm = 1 there
-      }  // first <= k < j: emitted when the sweep left the bin
+    J.tail(i, -QF[i]);  // g_max QF_n(hv), added to every bin by the gather
+    const int j = (int)c[i].k + h - 1;  // open bin (-1: below the range, h: past it)
+    // bins below the sweep: dF/dm = 1 there (the tail)
+    auto q = J.at(1 + i, 0);
+    for (int k = 0; k < first[i]; ++k) {
+      J.put(1 + i, q, T(0));
+      J.step(1 + i, q);
+    }
+    // the open bin, then those above the sweep: dS/dm = 1 there
+    T v = j < 0 ? B[i] : c[i].id * Y[i];
+    q = J.at(1 + i, j < 0 ? 0 : j);
+    for (int k = j < 0 ? 0 : j; k < h; ++k) {
+      J.put(1 + i, q, v);
+      J.step(1 + i, q);
+      v = B[i];
     }
   }
   pmin = amin;
@@ -186,11 +204,75 @@ struct JPlanes {
   uint32_t EJ;
   int64_t sj;
   int h;
-  CP_HD int64_t at(int slot, int k) const { return (int64_t)((uint64_t)(uint32_t)(slot * h + k) * EJ) + sj; }
-  CP_HD void set(int slot, int k, T v) const { J[at(slot, k)] = v; }
-  CP_HD void tail(int i, T v) const { J[at(5, i)] = v; }  // plane 5 h + i
+  using At = T*;
+  CP_HD T* at(int slot, int k) const { return J + (int64_t)((uint64_t)(uint32_t)(slot * h + k) * EJ) + sj; }
+  CP_HD void step(int, T*& a) const { a += EJ; }
+  CP_HD void put(int, T* a, T v) const { *a = v; }
+  CP_HD void tail(int i, T v) const { *at(5, i) = v; }  // plane 5 h + i
 };
 
+// The same for a wave that holds 64 consecutive vertices of a row: what the
+// stencils of the row add to each other (slots v, e and w) is summed in LDS, G
+// [h][66] with a column on either side for the neighbours outside, and only
+// the sums, the entries for the rows above and below and the two edge columns
+// go to the workspace.  The lanes of a wave leave a bin at different times, so
+// every entry stored directly is a request of its own: 54 for a vertex of ten
+// bins, and the sweep waited on them for a third of its time.  One wave's LDS
+// operations run in order, so the sums are reproducible.
+template <typename T>
+struct JRow {
+  JPlanes<T> P;
+  T* G;
+  int lane;
+  T te, tw;  // tails of the e and w neighbour
+  static constexpr int GX = 66;
+  struct At {
+    T *g, *l;  // workspace or LDS, by slot
+  };
+  static __device__ __forceinline__ bool in_row(int slot) { return slot == 0 || slot == 1 || slot == 3; }
+  __device__ __forceinline__ At at(int slot, int k) const {
+    return {in_row(slot) ? nullptr : P.at(slot, k), G + k * GX + lane + 1 + (slot == 1 ? 1 : slot == 3 ? -1 : 0)};
+  }
+  __device__ __forceinline__ void step(int slot, At& a) const {
+    if (in_row(slot))
+      a.l += GX;
+    else
+      a.g += P.EJ;
+  }
+  __device__ __forceinline__ void put(int slot, const At& a, T v) const {
+    if (in_row(slot))
+      __hip_atomic_fetch_add(a.l, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    else
+      *a.g = v;
+  }
+  __device__ __forceinline__ void tail(int i, T v) {
+    if (i == 0)
+      te = v;
+    else if (i == 2)
+      tw = v;
+    else
+      P.tail(i, v);
+  }
+};
+
+// Whether the adjoint sums rows on chip (sweep and gather agree on it): eight
+// bins on, as far as the row buffers beside the staged planes leave the waves
+// that the registers allow, on fields whose workspace is past half of the
+// 256 MB last-level cache.  Direct entries depend on the data (how far the
+// lanes of a wave drift apart), row sums do not.  FP32, 1024^2, direct over
+// three ensembles and row sums: 6 bins 176-181 and 191 us, 8 bins 228-334 and
+// 241, 10 bins 281-434 and 300, 18 bins 606-933 and 620, 20 bins 702-1059 and
+// 893; 2048 x 1100 x 10 bins 631-860 and 670; 600 x 512 x 10 bins (66 MB)
+// 104-133 and 122.  FP64, 1024^2: 8 bins 474-501 and 445, 13 bins 729-841 and
+// 710, 16 bins 908-1035 and 1335.
+__host__ __device__ constexpr bool hist_rows_fit(int h, size_t el) { return h >= 8 && h <= (el == 4 ? 18 : 13); }
+__host__ __device__ constexpr bool hist_row_sums(int h, size_t el, int64_t vertices) {
+  return hist_rows_fit(h, el) && hist_ws_planes(h) * (int64_t)el * vertices >= (int64_t)128 << 20;
+}
+// LDS of a sweep tile (elements): staged planes, then a row buffer per wave
+__host__ __device__ constexpr size_t hist_sweep_lds(int h, int E, int nt, bool rows) {
+  return (size_t)hist_planes(h) * E + (rows ? (size_t)(nt / 64) * h * 66 : 0);
+}
 
 // Both sides of one stencil (centre e in the staged tile, grid position
 // (gy, gx)) into J; returns the probabilities; an invalid stencil emits NaN
@@ -206,11 +288,11 @@ __host__ __device__ void hist_stencil_jac(const HistLds<T>& L, const HistSuf<T>&
 #pragma unroll
   for (int k = 0; k < 4; ++k) ok = ok && (!pres[k] || L.valid(en[k]));
   if (!ok) {
-    for (int k = 0; k < h; ++k) J.set(0, k, qnan<T>());
+    for (int k = 0; k < h; ++k) J.put(0, J.at(0, k), qnan<T>());
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (pres[i]) {
-        for (int k = 0; k < h; ++k) J.set(1 + i, k, qnan<T>());
+        for (int k = 0; k < h; ++k) J.put(1 + i, J.at(1 + i, k), qnan<T>());
         J.tail(i, T(0));
       }
     pmin = pmax = qnan<T>();
@@ -244,6 +326,8 @@ __device__ __forceinline__ void tile_hist_sweep(const FieldPtrs<T>& f, int ty0, 
   hist_stage_suffix<T, NT>(lds, E, h, tid);
   __syncthreads();
   const int lx = tid % TX, x = tx0 + lx;
+  const bool rows = hist_row_sums(h, sizeof(T), (int64_t)f.H * f.W);
+  T* G = lds + (size_t)hist_planes(h) * E + (size_t)(tid / TX) * h * JRow<T>::GX;
   for (int ly = tid / TX; ly < TY; ly += NT / TX) {
     const int y = ty0 + ly;
     if (x < f.W && y < f.H) {
@@ -253,8 +337,37 @@ __device__ __forceinline__ void tile_hist_sweep(const FieldPtrs<T>& f, int ty0, 
       const int64_t sj = (int64_t)y * f.W + x;
       T pmin, pmax;
       JPlanes<T> Jo{J, (uint32_t)((int64_t)f.H * f.W), sj, h};
-      hist_stencil_jac(L, U, lds, E, EX, (ly + 1) * EX + lx + 1, y, x, f.H, f.W, f.gmin[at], f.gmax[at], Jo, pmin,
-                       pmax);
+      if (rows) {
+        // (the active lanes are the first of the wave)
+        const int n = f.W - tx0 < TX ? f.W - tx0 : TX;
+        for (int i = lx; i < h * JRow<T>::GX; i += n) G[i] = T(0);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        JRow<T> Jr{Jo, G, lx, T(0), T(0)};
+        hist_stencil_jac(L, U, lds, E, EX, (ly + 1) * EX + lx + 1, y, x, f.H, f.W, f.gmin[at], f.gmax[at], Jr, pmin,
+                         pmax);
+        // tails from the west and east neighbours' stencils in the row
+        T tails = T(0);
+        const T fw = __shfl_up(Jr.te, 1, 64), fe = __shfl_down(Jr.tw, 1, 64);
+        if (lx > 0) tails += fw;
+        if (lx < TX - 1 && x + 1 < f.W) tails += fe;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        T* to = Jo.at(0, 0);
+        const T* g = G + lx + 1;
+        for (int k = 0; k < h; ++k, to += Jo.EJ, g += JRow<T>::GX) *to = *g + tails;
+        // the columns beside the tile, at the stencils of its ends
+        if (lx == 0 && x > 0) {
+          Jo.tail(2, Jr.tw);
+          for (int k = 0; k < h; ++k) *Jo.at(3, k) = G[k * JRow<T>::GX];
+        }
+        if (lx == TX - 1 && x + 1 < f.W) {
+          Jo.tail(0, Jr.te);
+          for (int k = 0; k < h; ++k) *Jo.at(1, k) = G[k * JRow<T>::GX + TX + 1];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      } else {
+        hist_stencil_jac(L, U, lds, E, EX, (ly + 1) * EX + lx + 1, y, x, f.H, f.W, f.gmin[at], f.gmax[at], Jo, pmin,
+                         pmax);
+      }
       if (f.pmin) {
         f.pmin[at] = pmin;
         f.pmax[at] = pmax;
@@ -281,10 +394,14 @@ __device__ __forceinline__ void hist_gather_vertex(const FieldPtrs<T>& f, const 
   // of its east (west, north, south) neighbour
   const T te = x + 1 < f.W ? e(id + 1, 5, 2) : T(0), tw = x > 0 ? e(id - 1, 5, 0) : T(0);
   const T tn = y > 0 ? e(id - f.W, 5, 3) : T(0), ts = y + 1 < f.H ? e(id + f.W, 5, 1) : T(0);
+  // (a row summed on chip has its east and west entries but for the edges of
+  // the 64-vertex tiles)
+  const bool rows = hist_row_sums(h, sizeof(T), plane);
+  const bool ge = x + 1 < f.W && (!rows || (x + 1) % kFwdTX == 0), gw = x > 0 && (!rows || x % kFwdTX == 0);
   for (int k = 0; k < h; ++k) {
     T g = e(id, 0, k);
-    if (x + 1 < f.W) g += e(id + 1, 3, k) + te;
-    if (x > 0) g += e(id - 1, 1, k) + tw;
+    if (ge) g += e(id + 1, 3, k) + te;
+    if (gw) g += e(id - 1, 1, k) + tw;
     if (y > 0) g += e(id - f.W, 4, k) + tn;
     if (y + 1 < f.H) g += e(id + f.W, 2, k) + ts;
     f.grad[(int64_t)(2 + k) * f.ps + at] = g;
@@ -321,6 +438,26 @@ __device__ __forceinline__ void hist_gather_vec(const FieldPtrs<T>& f, const T* 
   };
   const Vec te = ld(5, 2, id + 1), tw = ld(5, 0, id - 1);
   const Vec tn = ld(5, 3, hasn ? id - f.W : id), ts = ld(5, 1, hass ? id + f.W : id);
+  if (hist_row_sums(h, sizeof(T), plane)) {
+    // east and west entries only at the edges of the 64-vertex tiles, which
+    // are edges of a thread's group
+    const bool ge = x + V < f.W && (x + V) % kFwdTX == 0, gw = x > 0 && x % kFwdTX == 0;
+    for (int k = 0; k < h; ++k) {
+      Vec g = *reinterpret_cast<const Vec*>(J + (int64_t)k * plane + id);
+      const Vec n = ld(4, k, hasn ? id - f.W : id), s = ld(2, k, hass ? id + f.W : id);
+      if (ge) g[V - 1] += J[(int64_t)(3 * h + k) * plane + id + V] + te[V - 1];
+      if (gw) g[0] += J[(int64_t)(h + k) * plane + id - 1] + tw[0];
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        T t = g[j];
+        if (hasn) t += n[j] + tn[j];
+        if (hass) t += s[j] + ts[j];
+        g[j] = t;
+      }
+      *reinterpret_cast<Vec*>(f.grad + (int64_t)(2 + k) * f.ps + at) = g;
+    }
+    return;
+  }
   for (int k = 0; k < h; ++k) {
     Vec g = *reinterpret_cast<const Vec*>(J + (int64_t)k * plane + id);
     const Vec e = ld(3, k, id + 1), w = ld(1, k, id - 1);
