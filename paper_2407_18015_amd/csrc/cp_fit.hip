@@ -31,11 +31,41 @@ namespace {
 
 constexpr int kFitTX = 64, kFitTY = 4, kMaxRegMembers = 32;
 
+// Bin of a member x of a vertex's range [lo, hi]: floor((x - lo) / (hi - lo) * nb),
+// clamped.  The quotient is correctly rounded; all members share the divisor,
+// so it is its rounded reciprocal's product, corrected twice by the exact
+// remainder (Markstein's scheme, as div_count), five operations.  A remainder
+// that underflows then belongs to a quotient below 2^-24: bin 0 either way.
+// Ranges outside the limits, infinite and NaN ones divide.
 template <typename T>
-__device__ __forceinline__ int bin_of(T x, T lo, T hi, int nb) {
-  const T t = rn_div(rn_sub(x, lo), rn_sub(hi, lo));
-  int j = (int)rn_mul(t, T(nb));
-  return j < 0 ? 0 : (j > nb - 1 ? nb - 1 : j);
+struct BinOf {
+  T lo, range, inv, fnb;
+  int nb;
+  bool exact;
+  __device__ __forceinline__ BinOf(T lo_, T hi, int nb_) : lo(lo_), range(rn_sub(hi, lo_)), fnb(T(nb_)), nb(nb_) {
+    constexpr T kLo = sizeof(T) == 8 ? T(1e-200) : T(1e-30f), kHi = sizeof(T) == 8 ? T(1e200) : T(1e30f);
+    exact = range >= kLo && range <= kHi;
+    inv = rn_div(T(1), range);
+  }
+  __device__ __forceinline__ int operator()(T x) const {
+    const T a = rn_sub(x, lo);
+    T t;
+    if (exact) {
+      t = rn_mul(a, inv);
+      t = fma(fma(-t, range, a), inv, t);
+      t = fma(fma(-t, range, a), inv, t);
+    } else {
+      t = rn_div(a, range);
+    }
+    const int j = (int)rn_mul(t, fnb);
+    return j < 0 ? 0 : (j > nb - 1 ? nb - 1 : j);
+  }
+};
+
+// one more in a thread's own counter: an LDS addition that returns nothing, so
+// the next member's does not wait for it
+__device__ __forceinline__ void count(int* c) {
+  __hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 struct FitArgs {
@@ -45,6 +75,7 @@ struct FitArgs {
   int64_t rs, ps;
   double wscale;  // bw * M^(-1/5) / sqrt(M - ddof): Epanechnikov w = wscale * sqrt(sum of squares)
   double eps;
+  double im;  // 1 / M
 };
 
 // Uniform / Epanechnikov / histogram.  MM (histogram): members held in
@@ -62,7 +93,7 @@ __global__ __launch_bounds__(kFitTX* kFitTY) void k_fit(FitArgs a) {
   const int M = a.M;
   if (MODEL != CP_HISTOGRAM) {
     T p0, p1;
-    fit_ue_vertex<T, MODEL>(mem, M, a.ps, at, a.wscale, a.eps, p0, p1);
+    fit_ue_vertex<T, MODEL>(mem, M, a.ps, at, a.im, a.wscale, a.eps, p0, p1);
     par[at] = p0;
     par[a.ps + at] = p1;
     return;
@@ -96,14 +127,15 @@ __global__ __launch_bounds__(kFitTX* kFitTY) void k_fit(FitArgs a) {
   }
   // histogram: per-thread counters in LDS (dynamic bin index)
   int* cnt = counts + tid;
+  const BinOf<T> bin(lo, hi, a.nb);
   constexpr int NT = kFitTX * kFitTY;
   for (int j = 0; j < a.nb; ++j) cnt[j * NT] = 0;
   if (MM > 0) {
 #pragma unroll
     for (int k = 0; k < (MM > 0 ? MM : 1); ++k)
-      if (k < M) cnt[bin_of(v[k], lo, hi, a.nb) * NT] += 1;
+      if (k < M) count(cnt + bin(v[k]) * NT);
   } else {
-    for (int k = 0; k < M; ++k) cnt[bin_of(mem[(int64_t)k * a.ps + at], lo, hi, a.nb) * NT] += 1;
+    for (int k = 0; k < M; ++k) count(cnt + bin(mem[(int64_t)k * a.ps + at]) * NT);
   }
   par[at] = lo;
   par[a.ps + at] = hi;
@@ -145,7 +177,9 @@ __global__ __launch_bounds__(256) void k_fit_vec(FitArgs a, int64_t nvec) {
   }
   T r0[V], r1[V];
 #pragma unroll
-  for (int j = 0; j < V; ++j) acc[j].finish(a.M, a.wscale, a.eps, r0[j], r1[j]);
+  for (int j = 0; j < V; ++j)
+    acc[j].finish(a.M, a.im, a.wscale, a.eps, r0[j], r1[j],
+                  [&](int k) { return mem[(int64_t)k * a.ps + at + j]; });
   Vec o0, o1;
 #pragma unroll
   for (int j = 0; j < V; ++j) {
@@ -325,6 +359,7 @@ hipError_t fit_params(const Field& f, const void* members, int M, int ddof, doub
   a.ps = f.plane();
   a.wscale = fit_wscale(f.model, M, ddof, bw);
   a.eps = eps;
+  a.im = 1.0 / (double)M;
   if (f.model == CP_MVGAUSS) {
     dim3 grid((a.W + kFitTX - 1) / kFitTX, (a.H + kFitTY - 1) / kFitTY);
     hipLaunchKernelGGL(k_fit_mean, grid, dim3(256), 0, st, a);

@@ -67,6 +67,19 @@ __device__ __forceinline__ T degenerate_half(T eps, T x) {
   return rn_mul(eps, x < T(0) ? (-x > T(1) ? -x : T(1)) : (x > T(1) ? x : T(1)));
 }
 
+// a / M, correctly rounded, with iM = 1 / M rounded: the quotient corrected
+// twice by its exact remainder (Markstein's scheme: the first correction leaves
+// at most one unit in the last place, the second then rounds correctly).  Five
+// operations against the fifteen of a division; values whose remainder could
+// underflow or overflow are divided.
+__device__ __forceinline__ double div_count(double a, double M, double iM) {
+  const double s = fabs(a);
+  if (!(s >= 1e-280 && s <= 1e300)) return a / M;
+  double q = a * iM;
+  q = fma(fma(-q, M, a), iM, q);
+  return fma(fma(-q, M, a), iM, q);
+}
+
 // Running statistics of one vertex's members, then its parameters.
 // Uniform: (lo, hi) = (min, max); Epanechnikov / Gaussian: (m, w) with
 // w = wscale * sqrt(sum of squared deviations).  Every fit kernel feeds the
@@ -78,12 +91,15 @@ __device__ __forceinline__ T degenerate_half(T eps, T x) {
 // x0 exactly when some |d| > 0 (the difference of two distinct values of the
 // field's type is never 0 in FP64).  A NaN member gives a NaN d, which the
 // test ignores, as the min / max comparisons ignore it; a NaN first member
-// makes every d NaN: degenerate, as !(min < max) is then.
+// makes every d NaN: degenerate, as !(min < max) is then.  In FP32 no square of
+// a d underflows, so the sum of squares tells as much without a comparison per
+// member; only where it is NaN are the members (member(k)) looked at again.
 template <typename T, int MODEL>
 struct FitAcc {
   T mn, mx;
   double shift, s1, s2;
   bool spread;
+  static constexpr bool kBySquares = sizeof(T) == 4;
   __device__ __forceinline__ void first(T x0) {
     if (MODEL == CP_UNIFORM) {
       mn = mx = x0;
@@ -99,12 +115,14 @@ struct FitAcc {
       mx = xk > mx ? xk : mx;
     } else {
       const double d = (double)xk - shift;
-      spread = spread || fabs(d) > 0.0;
+      if (!kBySquares) spread = spread || fabs(d) > 0.0;
       s1 += d;
       s2 = fma(d, d, s2);
     }
   }
-  __device__ __forceinline__ void finish(int M, double wscale, double eps, T& p0, T& p1) const {
+  // iM = 1 / M
+  template <typename Member>
+  __device__ __forceinline__ void finish(int M, double iM, double wscale, double eps, T& p0, T& p1, Member member) {
     if (MODEL == CP_UNIFORM) {
       if (!(mn < mx)) {
         const T e = degenerate_half(T(eps), mn);
@@ -116,12 +134,17 @@ struct FitAcc {
       }
       return;
     }
-    const double mean = shift + s1 / (double)M;
+    if (kBySquares) {
+      spread = s2 > 0.0;
+      if (s2 != s2)
+        for (int k = 1; k < M; ++k) spread = spread || fabs((double)member(k) - shift) > 0.0;
+    }
+    const double mean = shift + div_count(s1, (double)M, iM);
     double w;
     if (!spread) {
       w = eps * fmax(1.0, fabs(mean));
     } else {
-      const double ss = fmax(s2 - s1 * s1 / (double)M, 0.0);
+      const double ss = fmax(s2 - div_count(s1 * s1, (double)M, iM), 0.0);
       w = wscale * sqrt(ss);
     }
     p0 = (T)mean;
@@ -132,13 +155,13 @@ struct FitAcc {
 // Parameters (p0, p1) of one vertex from its M members, member k at
 // mem[at + k*ps].
 template <typename T, int MODEL>
-__device__ __forceinline__ void fit_ue_vertex(const T* __restrict__ mem, int M, int64_t ps, int64_t at,
+__device__ __forceinline__ void fit_ue_vertex(const T* __restrict__ mem, int M, int64_t ps, int64_t at, double iM,
                                               double wscale, double eps, T& p0, T& p1) {
   FitAcc<T, MODEL> acc;
   acc.first(mem[at]);
 #pragma unroll 4
   for (int k = 1; k < M; ++k) acc.add(mem[(int64_t)k * ps + at]);
-  acc.finish(M, wscale, eps, p0, p1);
+  acc.finish(M, iM, wscale, eps, p0, p1, [&](int k) { return mem[(int64_t)k * ps + at]; });
 }
 
 }  // namespace cp
