@@ -193,11 +193,11 @@ CP_HD T qnan() {
 // Selection by a mask of ones or zeros: a < b as a subtraction and a shift,
 // and m ? a : b as one v_bitop3_b32, issue in half the cycles of v_cmp and
 // v_cndmask on gfx950.  Keys are not NaN; equal keys may give either mask.
-CP_HD uint32_t less_mask(float a, float b) {
-  return (uint32_t)(__builtin_bit_cast(int32_t, a - b) >> 31);
-}
-CP_HD uint32_t less_mask(double a, double b) {
-  return (uint32_t)((int32_t)(__builtin_bit_cast(uint64_t, a - b) >> 32) >> 31);
+CP_HD uint32_t sign_mask(float a) { return (uint32_t)(__builtin_bit_cast(int32_t, a) >> 31); }
+CP_HD uint32_t sign_mask(double a) { return (uint32_t)((int32_t)(__builtin_bit_cast(uint64_t, a) >> 32) >> 31); }
+template <typename T>
+CP_HD uint32_t less_mask(T a, T b) {
+  return sign_mask(a - b);
 }
 CP_HD uint32_t sel_bits(uint32_t m, uint32_t a, uint32_t b) {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -36,12 +36,16 @@
 // Both kinds run through one node loop, so a wave that holds both pays the
 // longer of the two, not their sum.
 //
-// Bound by vector issue (the tails: one reciprocal, one exponential and nine
-// fused multiply-adds each).  Measured at 1024^2 on a 20-member fit, FP32,
-// composite rule for every vertex -> this: classification 544 -> 92 us,
-// adjoint 1156 -> 161 us; at 512^2 in FP64 with sigmas within a factor of two
-// 2.16 -> 0.25 and 3.85 -> 0.44 ms.  Sigmas drawn over a factor of 300 (most
-// waves then hold composite vertices): 165 -> 164 and 564 -> 455 us at 512^2.
+// Bound by vector issue.  A tail is one reciprocal, one exponential and nine
+// fused multiply-adds in FP32; in FP64 a ratio of polynomials and the density's
+// own exponential: two nodes take 484 vector instructions (adjoint 530) against
+// 753 (983) with the library's erfc and exp.  Measured at 1024^2 on a 20-member fit, FP32,
+// composite rule for every vertex -> this: classification 544 -> 88 us,
+// adjoint 1156 -> 158 us.  Sigmas drawn over a factor of 300 (most
+// waves then hold composite vertices): 165 -> 136 and 564 -> 424 us at 512^2.
+// FP64 at 1024^2, sigmas within 20%, erfc and exp -> this: 638 -> 415 and
+// 1121 -> 617 us (the composite rule took 2.16 and 3.85 ms at 512^2); 512^2 over a factor of 300
+// 1646 -> 1097 and 3121 -> 1756 us.
 #pragma once
 
 #include <cmath>
@@ -59,27 +63,29 @@ struct GaussRule<float> {
   static constexpr int K = 7, N = 6;
   static constexpr float c[7] = {-6.f, -4.f, -2.f, 0.f, 2.f, 4.f, 6.f};
   static constexpr double hc = 1.07755;
-  static constexpr float scale = kTailScale;  // of a deviate in gauss_tail
 };
 template <>
 struct GaussRule<double> {
   static constexpr int K = 11, N = 10;
   static constexpr double c[11] = {-8.5, -6.0, -4.5, -3.0, -1.5, 0.0, 1.5, 3.0, 4.5, 6.0, 8.5};
   static constexpr double hc = 0.78539816339744830962;
-  static constexpr double scale = 0.70710678118654752440;
 };
 
-// Normal density factor and upper tail of |z| from the scaled deviate
-// zs = z GaussRule::scale: e = exp(-z^2 / 2), q = Pr(N(0,1) > |z|).  FP32 in the
-// hardware-instruction form of cp_mc_math.hpp (the exponential is shared);
-// FP64: the C library.
-CP_HD void gauss_tail(float zs, float& q, float& e) { upper_tail(zs, q, e); }
-CP_HD void gauss_tail(double zs, double& q, double& e) {
-  q = 0.5 * erfc(fabs(zs));
-  e = exp(-zs * zs);
+// S = Pr(neighbour above) and F = 1 - S from z's sign and its tail q, by the
+// sign's mask (an arithmetic shift and bit selections, which issue at twice the
+// rate of a comparison and conditional moves)
+template <typename T>
+CP_HD void gauss_sides(T z, T q, T& S, T& F) {
+  const uint32_t neg = sign_mask(z);
+  const T c = T(1) - q;
+  S = sel(neg, c, q);
+  F = sel(neg, q, c);
 }
-CP_HD float gauss_density(float zs) { return exp2_neg(-zs * zs); }
-CP_HD double gauss_density(double zs) { return exp(-zs * zs); }
+// normal density factor exp(-z^2 / 2) of the scaled deviate zs = z kTailScale
+template <typename T>
+CP_HD T gauss_density(T zs) {
+  return exp2_neg(-zs * zs);
+}
 
 // A stencil in vertex units and its rule; P: the type of z_n = (t - d) rs
 // (rs = r times the rule's scale).  An absent neighbour has rs = 0, so it sits at its
@@ -95,7 +101,7 @@ struct GaussPlan {
   // cut ck of neighbour n (any nearby point serves as well: held in T)
   CP_HD T cut(int n, T ck) const { return cfma(ck, s[n], T(d[n])); }
   // x in deviations of neighbour n
-  CP_HD T dev(int n, T x) const { return (x - T(d[n])) * T(rs[n]) * (T(1) / GaussRule<T>::scale); }
+  CP_HD T dev(int n, T x) const { return (x - T(d[n])) * T(rs[n]) * T(1.0 / kTailScale); }
 
   // The smallest cut of neighbour n above x0, C if there is none.  FP32: the
   // cuts lie two deviations apart, so it is found from x0's own deviation, to
@@ -152,7 +158,7 @@ CP_HD void gauss_plan(GaussPlan<T, P>& g, T mv, T sv, const T (&mn)[4], const T 
     const P r = pres[n] ? P(sv) / P(sn[n]) : P(0);
     g.d[n] = pres[n] ? (P(mn[n]) - P(mv)) * isv : P(4) * P(C);
     g.s[n] = pres[n] ? T(P(sn[n]) * isv) : T(0);
-    g.rs[n] = r * P(GaussRule<T>::scale);
+    g.rs[n] = r * P(kTailScale);
     // constant on the window: no bandwidth
     if (g.cut(n, -C) < C && g.cut(n, C) > -C) V = cfma(T(r), T(r), V);
   }
@@ -225,18 +231,18 @@ CP_HD void gauss_vertex(T mv, T sv, const T (&mn)[4], const T (&sn)[4], const bo
   GaussPlan<T, T> g;
   gauss_plan(g, mv, sv, mn, sn, pres);
   T acc[4] = {T(0), T(0), T(0), T(0)};
+  const T slope = vconst(T(kTailSlope));
   const auto node = [&](T, T t, T w) {
     T S[4], F[4];
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
       const T z = (t - g.d[n]) * g.rs[n];
       T q, e;
-      gauss_tail(z, q, e);
-      S[n] = z > T(0) ? q : T(1) - q;
-      F[n] = z > T(0) ? T(1) - q : q;
+      upper_tail(z, slope, q, e);
+      gauss_sides(z, q, S[n], F[n]);
     }
     // e, w (n = 0, 2) take S in t1 and F in t2; n, s the reverse
-    const T phi = w * gauss_density(t * GaussRule<T>::scale);
+    const T phi = w * gauss_density(t * T(kTailScale));
     const T sa = phi * (S[0] * S[2]), fa = phi * (F[0] * F[2]), sb = S[1] * S[3], fb = F[1] * F[3];
     acc[0] = cfma(sa, sb, acc[0]);
     acc[1] = cfma(fa, fb, acc[1]);
@@ -283,16 +289,17 @@ CP_HD void gauss_vertex_jac(T mv, T sv, const T (&mn)[4], const T (&sn)[4], cons
   P a[4] = {P(0), P(0), P(0), P(0)}, b[4] = {P(0), P(0), P(0), P(0)};
   T qa[4] = {T(0), T(0), T(0), T(0)}, qb[4] = {T(0), T(0), T(0), T(0)};
   const T ngmax = -gmax;
+  // FP32: z_n as one FP64 FMA (d_n rs_n rounds far below z_n's own FP32)
+  const P nd[4] = {-g.d[0] * g.rs[0], -g.d[1] * g.rs[1], -g.d[2] * g.rs[2], -g.d[3] * g.rs[3]};
   const auto node = [&](P tp, T t, T w) {
-    const T phi = w * gauss_density(t * GaussRule<T>::scale);
+    const T phi = w * gauss_density(t * T(kTailScale));
     T S[4], F[4], z[4], e[4];
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      z[n] = T((tp - g.d[n]) * g.rs[n]);
+      z[n] = sizeof(T) == 4 ? T(cfma(tp, g.rs[n], nd[n])) : T((tp - g.d[n]) * g.rs[n]);
       T q;
-      gauss_tail(z[n], q, e[n]);
-      S[n] = z[n] > T(0) ? q : T(1) - q;
-      F[n] = z[n] > T(0) ? T(1) - q : q;
+      upper_tail(z[n], T(kTailSlope), q, e[n]);
+      gauss_sides(z[n], q, S[n], F[n]);
     }
     // the pair products carry the node weight, the vertex density and the
     // upstream weight
@@ -326,7 +333,7 @@ CP_HD void gauss_vertex_jac(T mv, T sv, const T (&mn)[4], const T (&sn)[4], cons
     if (!pres[n]) continue;
     const P c = scale / P(sn[n]);
     const P dmu = c * a[n];  // g-weighted dP/dmu_n
-    const P dsg = c / P(GaussRule<T>::scale) * b[n];  // g-weighted dP/dsigma_n
+    const P dsg = c / P(kTailScale) * b[n];  // g-weighted dP/dsigma_n
     jac[2 + 2 * n] = T(dmu);
     jac[3 + 2 * n] = T(dsg);
     smu += dmu;

@@ -53,11 +53,13 @@ __host__ __device__ __forceinline__ float exp2_neg(float y) {
 #endif
 }
 
-constexpr float kTailScale = 0.84932180028801904f;  // sqrt(log2(e) / 2)
+constexpr double kTailScale = 0.84932180028801904272;  // sqrt(log2(e) / 2)
 
-// From zs = kTailScale z: e = exp(-z^2 / 2), q = Pr(N(0, 1) > |z|) = t p8(t) e
-__host__ __device__ __forceinline__ void upper_tail(float zs, float& q, float& e) {
-  const float u = __builtin_fmaf(0.30804520612834824f, __builtin_fabsf(zs), 1.0f);
+// From zs = kTailScale z: e = exp(-z^2 / 2), q = Pr(N(0, 1) > |z|) = t p8(t) e;
+// slope = kTailSlope (in a vector register it issues at full rate)
+constexpr float kTailSlope = 0.30804520612834824f;
+__host__ __device__ __forceinline__ void upper_tail(float zs, float slope, float& q, float& e) {
+  const float u = __builtin_fmaf(slope, __builtin_fabsf(zs), 1.0f);
 #if defined(__HIP_DEVICE_COMPILE__)
   const float t = __builtin_amdgcn_rcpf(u);
 #else
@@ -74,6 +76,64 @@ __host__ __device__ __forceinline__ void upper_tail(float zs, float& q, float& e
   p = __builtin_fmaf(p, t, 0.10366847941107675f);
   p = __builtin_fmaf(p, t, 0.10440969988813159f);
   q = p * t * e;
+}
+
+// FP64: 2^y for -1e4 < y <= 0 (or NaN).  y = n + f with |f| <= 1/2, 2^f = 1 +
+// f p10(f) (interpolated at Chebyshev points, 2e-17).
+__host__ __device__ __forceinline__ double exp2_neg(double y) {
+  const double n = __builtin_rint(y), f = y - n;
+  double p = 4.4549605981865186e-10;
+  p = __builtin_fma(p, f, 7.072585949269223e-09);
+  p = __builtin_fma(p, f, 1.0178062445845774e-07);
+  p = __builtin_fma(p, f, 1.321544258792169e-06);
+  p = __builtin_fma(p, f, 1.525273382983612e-05);
+  p = __builtin_fma(p, f, 0.0001540353044173605);
+  p = __builtin_fma(p, f, 0.0013333558146416936);
+  p = __builtin_fma(p, f, 0.009618129107606888);
+  p = __builtin_fma(p, f, 0.0555041086648216);
+  p = __builtin_fma(p, f, 0.24022650695910097);
+  p = __builtin_fma(p, f, 0.6931471805599453);
+  return __builtin_ldexp(__builtin_fma(f, p, 1.0), (int)n);
+}
+
+// FP64, from the same zs: q = e p8(x) / p9(x) with x = |zs|, the ratio
+// interpolating exp(z^2 / 2) Pr(N(0, 1) > z) at Chebyshev points of (z - 3 sqrt 2)
+// / (z + 3 sqrt 2) over z <= 9.9 (3e-17; 1e-10 at z = 28, where q is 1e-173).
+// All coefficients are positive, so both polynomials lose no digits.  Half the
+// work of erfc and exp, which evaluate every range of z that a wave holds and
+// the exponential twice.
+__host__ __device__ __forceinline__ void upper_tail(double zs, double, double& q, double& e) {
+  double x = __builtin_fabs(zs);
+  x = x > 33.0 ? 33.0 : x;  // 2^-x^2 is 0 from here on
+  e = exp2_neg(-x * x);
+  double n = 1.6082765204010446e-05;
+  n = __builtin_fma(n, x, 0.00034988923535707203);
+  n = __builtin_fma(n, x, 0.003639910750331352);
+  n = __builtin_fma(n, x, 0.02342658443092272);
+  n = __builtin_fma(n, x, 0.10161629013929727);
+  n = __builtin_fma(n, x, 0.30430775035359225);
+  n = __builtin_fma(n, x, 0.6177961374727721);
+  n = __builtin_fma(n, x, 0.7876151126824155);
+  n = __builtin_fma(n, x, 0.5);
+  double d = 4.746553494444576e-05;
+  d = __builtin_fma(d, x, 0.0010326383725138887);
+  d = __builtin_fma(d, x, 0.010776812870550278);
+  d = __builtin_fma(d, x, 0.06988448654069497);
+  d = __builtin_fma(d, x, 0.3076023397021155);
+  d = __builtin_fma(d, x, 0.9469179733868519);
+  d = __builtin_fma(d, x, 2.0285868500055297);
+  d = __builtin_fma(d, x, 2.9048174912382168);
+  d = __builtin_fma(d, x, 2.5146675040644864);
+  d = __builtin_fma(d, x, 1.0);
+#if defined(__HIP_DEVICE_COMPILE__)
+  // reciprocal to 2^-24, one Newton step, and the quotient corrected by its remainder
+  double r = __builtin_amdgcn_rcp(d);
+  r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+  const double a = n * r;
+  q = __builtin_fma(__builtin_fma(-d, a, n), r, a) * e;
+#else
+  q = n / d * e;
+#endif
 }
 
 // The tail alone for the Monte Carlo estimators, e kept to itself: p7 fitted

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void k_mvg_fwd(MvgArgs a) {
     load_stencil<true>(a, min(v0 + u, nv - 1), lane, s[u]);
     // r in upper_tail's scale; without neighbours both rows' extremes are +inf
     // and both estimates 1
-    inv[u] = kTailScale / s[u].L44;
+    inv[u] = float(kTailScale) / s[u].L44;
     invm[u] = s[u].first < 4 ? -inv[u] : inv[u];
     qmin[u] = qmax[u] = 0.0;
     nmin[u] = nmax[u] = 0;
