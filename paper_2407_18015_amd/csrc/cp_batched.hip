@@ -50,7 +50,7 @@ namespace cp {
 namespace {
 
 constexpr int kNT = 256;
-constexpr int kGatherChunk = 256;          // histogram gather: vertices per tile
+constexpr int kGatherChunk = 256;          // histogram gather: groups of vertices per tile
 constexpr size_t kMaxLds = 160 * 1024;
 
 enum { PASS_FWD_UE = 0, PASS_FWD_HIST = 1, PASS_BWD_UE = 2, PASS_BWD_HIST = 3, PASS_GATHER = 4, NPASS = 5 };
@@ -69,7 +69,7 @@ __host__ __device__ constexpr int bwd_ox(bool f32, int v) { return f32 ? (v == 2
 __host__ __device__ constexpr int bwd_oy(bool f32, int v) { return f32 ? (v == 1 ? 14 : 30) : (v == 2 ? 30 : 14); }
 
 struct BatchTile {
-  int field, ty0, tx0, pad;  // gather tiles: ty0 = first flat vertex index
+  int field, ty0, tx0, pad;  // gather tiles: ty0 = first flat group index
 };
 
 template <typename T>
@@ -115,7 +115,10 @@ __device__ __forceinline__ void batched_tile(const BatchField<T>* __restrict__ f
   } else if constexpr (PASS == PASS_BWD_HIST) {
     tile_hist_sweep<T, TY, kNT>(F.p, tl.ty0, tl.tx0, lds, tid, F.J);
   } else {
-    hist_gather_vertex<T>(F.p, F.J, (int64_t)tl.ty0 + tid);
+    if (F.p.W >= gather_vec<T>())
+      hist_gather_vec<T>(F.p, F.J, (int64_t)tl.ty0 + tid);
+    else
+      hist_gather_vertex<T>(F.p, F.J, (int64_t)tl.ty0 + tid);
   }
 }
 
@@ -332,8 +335,9 @@ void pass_tiles(const std::vector<Field>& fs, int pass, int v, size_t el, std::v
     if (!mine) continue;
     lds = std::max(lds, tile_lds_bytes(pass, v, f, el));
     if (pass == PASS_GATHER) {
-      const int64_t plane = (int64_t)f.H * f.W;
-      for (int64_t t = 0; t < plane; t += kGatherChunk) {
+      const int V = (int)(16 / el);
+      const int64_t threads = gather_groups(f.H, f.W, f.W >= V ? V : 1);
+      for (int64_t t = 0; t < threads; t += kGatherChunk) {
         tiles.push_back(BatchTile{i, (int)t, 0, 0});
         cost.push_back(1.0);
       }

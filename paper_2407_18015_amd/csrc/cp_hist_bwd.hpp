@@ -409,29 +409,38 @@ __device__ __forceinline__ void hist_gather_vertex(const FieldPtrs<T>& f, const 
 }
 
 // The same gather for V = 16 / sizeof(T) vertices of one row per thread
-// (W, the row stride and the plane stride multiples of V, grad 16-byte
-// aligned): the own and north / south entries are aligned vector loads, the
-// east / west ones the same vectors shifted by one vertex (4-byte aligned
-// loads; at a row end the lane takes no entry, and every address stays
-// inside the workspace: the shifted rows of slots 1 and 3, of the tail planes
-// and the rows above / below of slots 4 and 2 lie between plane 1 and the
-// last tail plane).  Terms are added in the scalar gather's order and absent
-// ones skipped, so the sums are bit-identical to it.
+// (W >= V): group q covers V vertices of row q / ceil(W / V), the last of a row
+// its last V, so that some of them are gathered twice where V does not divide W
+// (by the same operations, to the same values).  Vectors are at element
+// alignment: the own and north / south entries, and the east / west ones
+// shifted by one vertex (at a row end the lane takes no entry, and every
+// address stays inside the workspace: the shifted rows of slots 1 and 3, of the
+// tail planes and the rows above / below of slots 4 and 2 lie between plane 1
+// and the last tail plane).  Terms are added in the scalar gather's order and
+// absent ones skipped, so the sums are bit-identical to it.
+template <typename T>
+__host__ __device__ constexpr int gather_vec() {
+  return 16 / (int)sizeof(T);
+}
+__host__ __device__ constexpr int64_t gather_groups(int H, int W, int V) { return (int64_t)H * ((W + V - 1) / V); }
+
 template <typename T>
 __device__ __forceinline__ void hist_gather_vec(const FieldPtrs<T>& f, const T* __restrict__ J, int64_t q) {
-  constexpr int V = 16 / sizeof(T);
+  constexpr int V = gather_vec<T>();
   typedef T Vec __attribute__((ext_vector_type(V)));
+  if (q >= gather_groups(f.H, f.W, V)) return;
   const int64_t plane = (int64_t)f.H * f.W;
-  const int64_t id = q * V;
-  if (id >= plane) return;
-  const int y = (int)(id / f.W), x = (int)(id - (int64_t)y * f.W);
+  const int gr = (f.W + V - 1) / V;
+  const int y = (int)(q / gr), g0 = (int)(q - (int64_t)y * gr) * V, x = g0 < f.W - V ? g0 : f.W - V;
+  const int64_t id = (int64_t)y * f.W + x;
   const int h = f.nb;
   const int64_t at = (int64_t)y * f.rs + x;
+  const auto st = [&](int64_t v, const Vec& r) { __builtin_memcpy(f.grad + v, &r, sizeof(Vec)); };
   const Vec z = Vec(T(0));
-  *reinterpret_cast<Vec*>(f.grad + at) = z;
-  *reinterpret_cast<Vec*>(f.grad + f.ps + at) = z;
+  st(at, z);
+  st(f.ps + at, z);
   const bool hasn = y > 0, hass = y + 1 < f.H;
-  const auto ld = [&](int slot, int k, int64_t v) {  // V entries from vertex v on (v 4-byte aligned)
+  const auto ld = [&](int slot, int k, int64_t v) {  // V entries from vertex v on
     Vec r;
     __builtin_memcpy(&r, J + (int64_t)(slot * h + k) * plane + v, sizeof(Vec));
     return r;
@@ -439,27 +448,31 @@ __device__ __forceinline__ void hist_gather_vec(const FieldPtrs<T>& f, const T* 
   const Vec te = ld(5, 2, id + 1), tw = ld(5, 0, id - 1);
   const Vec tn = ld(5, 3, hasn ? id - f.W : id), ts = ld(5, 1, hass ? id + f.W : id);
   if (hist_row_sums(h, sizeof(T), plane)) {
-    // east and west entries only at the edges of the 64-vertex tiles, which
-    // are edges of a thread's group
-    const bool ge = x + V < f.W && (x + V) % kFwdTX == 0, gw = x > 0 && x % kFwdTX == 0;
+    // east and west entries only at the edges of the 64-vertex tiles: vertex
+    // x + je has one to its east (none: je = V), x + jw to its west
+    const int r = x % kFwdTX, je = r + V < kFwdTX || x - r + kFwdTX >= f.W ? V : kFwdTX - 1 - r;
+    const int jw = r == 0 ? (x > 0 ? 0 : V) : (r + V > kFwdTX ? kFwdTX - r : V);
     for (int k = 0; k < h; ++k) {
-      Vec g = *reinterpret_cast<const Vec*>(J + (int64_t)k * plane + id);
+      Vec g = ld(0, k, id);
       const Vec n = ld(4, k, hasn ? id - f.W : id), s = ld(2, k, hass ? id + f.W : id);
-      if (ge) g[V - 1] += J[(int64_t)(3 * h + k) * plane + id + V] + te[V - 1];
-      if (gw) g[0] += J[(int64_t)(h + k) * plane + id - 1] + tw[0];
+      T e = T(0), w = T(0);
+      if (je < V) e = J[(int64_t)(3 * h + k) * plane + id + je + 1];
+      if (jw < V) w = J[(int64_t)(h + k) * plane + id + jw - 1];
 #pragma unroll
       for (int j = 0; j < V; ++j) {
         T t = g[j];
+        if (j == je) t += e + te[j];
+        if (j == jw) t += w + tw[j];
         if (hasn) t += n[j] + tn[j];
         if (hass) t += s[j] + ts[j];
         g[j] = t;
       }
-      *reinterpret_cast<Vec*>(f.grad + (int64_t)(2 + k) * f.ps + at) = g;
+      st((int64_t)(2 + k) * f.ps + at, g);
     }
     return;
   }
   for (int k = 0; k < h; ++k) {
-    Vec g = *reinterpret_cast<const Vec*>(J + (int64_t)k * plane + id);
+    Vec g = ld(0, k, id);
     const Vec e = ld(3, k, id + 1), w = ld(1, k, id - 1);
     const Vec n = ld(4, k, hasn ? id - f.W : id), s = ld(2, k, hass ? id + f.W : id);
 #pragma unroll
@@ -471,7 +484,7 @@ __device__ __forceinline__ void hist_gather_vec(const FieldPtrs<T>& f, const T* 
       if (hass) t += s[j] + ts[j];
       g[j] = t;
     }
-    *reinterpret_cast<Vec*>(f.grad + (int64_t)(2 + k) * f.ps + at) = g;
+    st((int64_t)(2 + k) * f.ps + at, g);
   }
 }
 
