@@ -151,17 +151,31 @@ static hipError_t launch_bwd_ue(const FieldPtrs<T>& p, int model, hipStream_t st
   return hipGetLastError();
 }
 
-// independent Gaussian: FP32 30x30 outputs (32x32 stencils, four per
-// thread), so the ring of halo stencils is 12% of the work against 24% for
-// 14x14; FP64 keeps 14x14 (one stencil per thread: its 239 registers leave
-// no room for a second)
-template <typename T>
+template <typename T, int OX, int OY>
 static hipError_t launch_bwd_gauss(const FieldPtrs<T>& p, hipStream_t st) {
-  constexpr int O = sizeof(T) == 4 ? 30 : 14;
-  const int tx = cdiv(p.W, O), ty = cdiv(p.H, O), n = tx * ty;
-  hipLaunchKernelGGL((k_bwd_ue<T, CP_GAUSSIAN, O, O>), dim3(n), dim3(256), 0, st, p, tx, n);
+  const int tx = cdiv(p.W, OX), ty = cdiv(p.H, OY), n = tx * ty;
+  hipLaunchKernelGGL((k_bwd_ue<T, CP_GAUSSIAN, OX, OY>), dim3(n), dim3(256), 0, st, p, tx, n);
   return hipGetLastError();
 }
+
+// FP32 adjoint tiles by the number of 30x30-output tiles (32x32 stencils, four
+// per thread; static LDS 32 KB, four resident per CU).  They compute the fewest
+// halo stencils (12% of the work; 30x14, two per thread, 17%; 14x14, one, 24%),
+// but a grid with few of them leaves most of the CUs' waves unused and ends on
+// blocks that run alone.  Adjoint in us, 14x14 / 30x14 / 30x30:
+//   Epanechnikov  200^2 5.1 / 9.6 / 19.3, 500^2 (289 tiles) 13.7 / 14.3 / 17.8,
+//     600^2 (400) 16.4 / 16.2 / 17.5, 720^2 (576) 23.5 / 21.8 / 25.2,
+//     900^2 (900) 31.5 / 28.9 / 30.8, 960^2 (1024) 34.0 / 32.1 / 31.0,
+//     1150^2 (1521) 47.7 / 44.8 / 43.2;
+//   uniform  200^2 3.7 / 5.4 / 9.0, 500^2 7.6 / 8.2 / 10.8, 720^2 12.4 / 11.5 /
+//     14.2, 960^2 19.0 / 18.0 / 17.7;
+//   Gaussian  200^2 19 / 32 / 62, 500^2 51 / 62 / 83, 840^2 (784) 114 / 122 / 141,
+//     1020^2 (1156) 160 / 168 / 173, 1150^2 203 / 214 / 204, 1250^2 (1764) 237 /
+//     245 / 232.
+// The shape changes no per-vertex operation: the same bits.  FP64 takes 14x14
+// throughout (Gaussian: its 241 registers leave no room for a second stencil).
+static int64_t tiles30(int H, int W) { return (int64_t)cdiv(W, 30) * cdiv(H, 30); }
+constexpr int64_t kBwdSmall = 448, kBwdMid = 960, kBwdGaussSmall = 1536;
 
 template <typename T, int TY>
 static hipError_t launch_bwd_hist(const FieldPtrs<T>& p, hipStream_t st, const Scratch& scr) {
@@ -193,14 +207,18 @@ template <typename T>
 static hipError_t bwd_typed(const Field& f, const void* params, const void* gmin, const void* gmax, void* grad,
                             hipStream_t st, const Scratch& scr) {
   FieldPtrs<T> p = make_ptrs<T>(f, params, nullptr, nullptr, gmin, gmax, grad);
-  if (f.model == CP_GAUSSIAN) return launch_bwd_gauss<T>(p, st);
-  if (f.model != CP_HISTOGRAM) {
-    // 30x30 outputs (32x32 stencils, 4 per thread) keep the FP32 tile under
-    // 64 KiB of static LDS; FP64 uses 14x14 (16x16 stencils)
+  const int64_t n30 = tiles30(p.H, p.W);
+  if (f.model == CP_GAUSSIAN) {
     if constexpr (sizeof(T) == 4)
-      return launch_bwd_ue<T, 30, 30>(p, f.model, st);
-    else
-      return launch_bwd_ue<T, 14, 14>(p, f.model, st);
+      if (n30 >= kBwdGaussSmall) return launch_bwd_gauss<T, 30, 30>(p, st);
+    return launch_bwd_gauss<T, 14, 14>(p, st);
+  }
+  if (f.model != CP_HISTOGRAM) {
+    if constexpr (sizeof(T) == 4) {
+      if (n30 >= kBwdMid) return launch_bwd_ue<T, 30, 30>(p, f.model, st);
+      if (n30 >= kBwdSmall) return launch_bwd_ue<T, 30, 14>(p, f.model, st);
+    }
+    return launch_bwd_ue<T, 14, 14>(p, f.model, st);
   }
   // sweep tiles as in the forward; the entries go through the workspace
   const size_t per_row = sizeof(T) * (size_t)hist_planes(f.nb) * (kFwdTX + 2);
