@@ -331,7 +331,8 @@ typedef enum {
  * Fix the tile shape and claim chunk of each pass of the plan that
  * cp_prob_batched uses for these descriptors and flags (building the plan if
  * no call has yet): shape[p] indexes the shapes listed under CP_BATCH_TUNE
- * for pass p (0 = the default), chunk[p] >= 1 tiles per claim of the
+ * for pass p (0 = the default; the FP32 uniform / Epanechnikov adjoint of few
+ * tiles: 1), chunk[p] >= 1 tiles per claim of the
  * persistent launch or -1 for one tile per block; entries < 0 (shape) or of
  * any other value (chunk) keep the current choice, entries of passes the
  * plan lacks are ignored.  For callers that tuned offline and want the result

@@ -402,6 +402,20 @@ cp_status_t build_pass(const Plan& P, int pass, int v, int chunk, Pass& out) {
 // it for every pass in most runs (histogram passes always)
 int default_chunk(int) { return 0; }
 
+// default tile shape: the first; the FP32 uniform / Epanechnikov adjoint of
+// fewer than 960 30x30 tiles in all takes 14x14 (one stencil per thread instead
+// of four), as large tiles leave most of the chip's waves unused.  Forward +
+// adjoint of 3, 5, 10 and 18 mixed fields with 25, 321, 524 and 823 such tiles:
+// 30x30 54, 72, 102 and 86 us, 14x14 44, 66, 96 and 84; 4799 and 10290 tiles
+// 527 and 960 against 534 and 981.
+int default_variant(int pass, const Plan& P) {
+  if (pass != PASS_BWD_UE || P.dtype != CP_F32) return 0;
+  int64_t n = 0;
+  for (const Field& f : P.fields)
+    if (f.model != CP_HISTOGRAM) n += (int64_t)((f.W + 29) / 30) * ((f.H + 29) / 30);
+  return n < 960 ? 1 : 0;
+}
+
 cp_status_t build_plan(int n, const Field* fs, bool bwd, Plan& P, const char** why) {
   const size_t el = fs[0].dtype == CP_F64 ? 8 : 4;
   P.dtype = fs[0].dtype;
@@ -431,7 +445,7 @@ cp_status_t build_plan(int n, const Field* fs, bool bwd, Plan& P, const char** w
   for (int q : {PASS_FWD_HIST, PASS_BWD_HIST, PASS_FWD_UE, PASS_BWD_UE, PASS_GATHER}) {
     if (!present[q]) continue;
     Pass Q;
-    cp_status_t s = build_pass(P, q, 0, default_chunk(q), Q);
+    cp_status_t s = build_pass(P, q, default_variant(q, P), default_chunk(q), Q);
     if (s == CP_EUNSUPPORTED) {
       *why = "batched: staged planes exceed the LDS of a workgroup (too many bins for this dtype)";
       return s;
