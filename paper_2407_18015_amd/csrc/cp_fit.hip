@@ -143,18 +143,17 @@ __global__ __launch_bounds__(kFitTX* kFitTY) void k_fit(FitArgs a) {
   for (int j = 0; j < a.nb; ++j) par[(int64_t)(2 + j) * a.ps + at] = rn_div(T(cnt[j * NT]), fm);
 }
 
-// Uniform / Epanechnikov with 16-byte loads: a thread fits V = 16 / sizeof(T)
-// consecutive vertices of a row, reading each member plane as one vector
-// (4 FP32 or 2 FP64 values).  On MI355X a stream of 16-byte loads reads HBM
+// Uniform / Epanechnikov with vector loads: a thread fits V consecutive vertices
+// of a row (16 bytes; 8 on the smallest FP32 grids), reading each member plane as
+// one vector, U members at a time (0: by fours, the remainder one by one).  On MI355X a stream of 16-byte loads reads HBM
 // at ~6.7 TB/s against ~4 TB/s for 4-byte loads.  Needs W, the row stride and
-// both base addresses multiples of V elements (the host checks).  The
+// both base addresses multiples of 16 bytes (the host checks).  The
 // per-vertex operations are FitAcc's, as in k_fit.
 // Members are read once and the parameters written once, so both go through
 // non-temporal accesses (no cache allocation on the way): 5.7 against
 // 5.0 TB/s for this access pattern at 2048^2 x 20.
-template <typename T, int MODEL>
+template <typename T, int MODEL, int V, int U>
 __global__ __launch_bounds__(256) void k_fit_vec(FitArgs a, int64_t nvec) {
-  constexpr int V = 16 / sizeof(T);
   typedef T Vec __attribute__((ext_vector_type(V)));
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= nvec) return;
@@ -169,11 +168,27 @@ __global__ __launch_bounds__(256) void k_fit_vec(FitArgs a, int64_t nvec) {
 #pragma unroll
     for (int j = 0; j < V; ++j) acc[j].first(v[j]);
   }
-#pragma unroll 4
-  for (int k = 1; k < a.M; ++k) {
-    const Vec v = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(mem + (int64_t)k * a.ps + at));
+  if constexpr (U > 0) {
+    for (int k0 = 1; k0 < a.M; k0 += U) {
+      Vec v[U];
 #pragma unroll
-    for (int j = 0; j < V; ++j) acc[j].add(v[j]);
+      for (int i = 0; i < U; ++i)
+        if (k0 + i < a.M)
+          v[i] = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(mem + (int64_t)(k0 + i) * a.ps + at));
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (k0 + i < a.M) {
+#pragma unroll
+          for (int j = 0; j < V; ++j) acc[j].add(v[i][j]);
+        }
+    }
+  } else {
+#pragma unroll 4
+    for (int k = 1; k < a.M; ++k) {
+      const Vec v = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(mem + (int64_t)k * a.ps + at));
+#pragma unroll
+      for (int j = 0; j < V; ++j) acc[j].add(v[j]);
+    }
   }
   T r0[V], r1[V];
 #pragma unroll
@@ -282,15 +297,37 @@ __global__ __launch_bounds__(256) void k_fit_mvg(FitArgs a, double jitter) {
     for (int c = 0; c <= r; ++c, ++t) par[(int64_t)(1 + t) * a.ps + at] = ok ? L[r][c] : __builtin_nan("");
 }
 
+// Small FP32 grids give the SIMDs a wave or two each, which wait for their
+// members: they fetch them eight at a time with no serial remainder, the
+// smallest as groups of two vertices (twice the waves).  20 members, in us, four
+// vertices by fours / by eights / two by eights:
+//   Epanechnikov  64^2 5.3 / 4.6 / 3.8, 500^2 (62500 groups of four) 7.4 / 6.0 /
+//     5.0, 600^2 13.6 / 8.0 / 7.0, 720^2 (129600) 12.4 / 7.7 / 8.4, 1000^2 (250000)
+//     16.7 / 13.9 / 14.2, 1200^2 (360000) 19.8 / 20.8 / 21.4, 2048^2 57 / 70 / 70;
+//   uniform  500^2 5.4 / 5.5 / 4.3, 600^2 7.2 / 6.9 / 6.3, 720^2 8.5 / 7.9 / 8.3,
+//     800^2 (160000) 9.8 / 9.5 / 10.1, 1000^2 12.6 / 13.1 / 13.9.
+// FP64 loses by eights at every size.
+constexpr int64_t kFitSmall = 98304, kFitMid = 262144, kFitMidUniform = 163840;
+
+template <typename T, int MODEL, int V, int U>
+hipError_t launch_fit_vec(const FitArgs& a, hipStream_t st) {
+  const int64_t nvec = (int64_t)a.H * (a.W / V);
+  hipLaunchKernelGGL((k_fit_vec<T, MODEL, V, U>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st, a, nvec);
+  return hipGetLastError();
+}
+
 template <typename T, int MODEL>
 hipError_t launch_fit(const FitArgs& a, hipStream_t st) {
   constexpr int V = 16 / sizeof(T);
   if constexpr (MODEL != CP_HISTOGRAM) {
     if (a.W % V == 0 && a.rs % V == 0 && reinterpret_cast<uintptr_t>(a.members) % 16 == 0 &&
         reinterpret_cast<uintptr_t>(a.params) % 16 == 0) {
-      const int64_t nvec = (int64_t)a.H * (a.W / V);
-      hipLaunchKernelGGL((k_fit_vec<T, MODEL>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st, a, nvec);
-      return hipGetLastError();
+      const int64_t n = (int64_t)a.H * (a.W / V);
+      if constexpr (sizeof(T) == 4) {
+        if (n <= kFitSmall) return launch_fit_vec<T, MODEL, 2, 8>(a, st);
+        if (n <= (MODEL == CP_UNIFORM ? kFitMidUniform : kFitMid)) return launch_fit_vec<T, MODEL, 4, 8>(a, st);
+      }
+      return launch_fit_vec<T, MODEL, V, 0>(a, st);
     }
   }
   dim3 grid((a.W + kFitTX - 1) / kFitTX, (a.H + kFitTY - 1) / kFitTY);

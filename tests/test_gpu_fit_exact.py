@@ -65,7 +65,8 @@ def test_histogram_bins(dt, nt, M, scale):
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64])
 @pytest.mark.parametrize("model", ["uniform", "epanechnikov"])
-@pytest.mark.parametrize("shape", [(5, 8), (9, 132), (13, 64), (1600, 2304)])  # both tile heights, remainders
+@pytest.mark.parametrize("shape", [(5, 8), (9, 132), (13, 64), (700, 800), (1600, 2304)])
+# (both tile heights, remainders, the fit's three loops)
 def test_fused_fit_is_the_fit(dt, model, shape):
     for M in (1, 2, 7, 9, 20) if shape[0] < 100 else (9,):
         if M == 1 and model == "epanechnikov":
