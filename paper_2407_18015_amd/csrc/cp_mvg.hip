@@ -55,12 +55,13 @@ struct MvgArgs {
 // (k = 0..3) issue beside the vector unit, which this kernel keeps busy: 1.61
 // against 1.81 ms with the 16 fused multiply-adds (500^2 x 2000).
 //
-// DIFF (the estimators): rows L_nk - L_4k, so the values are x_n - c,
+// DIFF (the conditional estimator): rows L_nk - L_4k, so the values are x_n - c,
 // differenced in FP64 and rounded once, with the deviates' kDeviateScale.
 // A row whose neighbour is absent repeats the first present one, which leaves
 // minimum and maximum as they are; without any neighbour all rows are +inf.
 //
-// Otherwise (the adjoint) the rows of L: each value is then the chain of FP32
+// Otherwise (the hit estimator, whose counts are whole numbers that a rounding
+// can change, and the adjoint) the rows of L: each value is then the chain of FP32
 // fused multiply-adds mu_n - mu_v + L_n0 z_0 + ... in the order of k.  A row
 // whose neighbour is absent is NaN, which minimum and maximum skip.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -131,12 +132,18 @@ __global__ __launch_bounds__(256) void k_mvg_fwd(MvgArgs a) {
   if (v0 >= nv) return;
   const PhiloxKeys keys = philox_keys(a.k0, a.k1);
   MvgStencil s[V];
-  float inv[V], invm[V];
+  float inv[V], invm[V], L4[HIT ? V : 1][4];
   double qmin[V], qmax[V];
   int nmin[V], nmax[V];
 #pragma unroll
   for (int u = 0; u < V; ++u) {
-    load_stencil<true>(a, min(v0 + u, nv - 1), lane, s[u]);
+    load_stencil<!HIT>(a, min(v0 + u, nv - 1), lane, s[u]);
+    if constexpr (HIT) {
+      const int v = min(v0 + u, nv - 1), y = v / a.W;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        L4[u][k] = (float)a.par[(int64_t)(11 + k) * a.ps + (int64_t)y * a.rs + (v - y * a.W)];
+    }
     // r in upper_tail's scale; without neighbours both rows' extremes are +inf
     // and both estimates 1
     inv[u] = float(kTailScale) / s[u].L44;
@@ -161,21 +168,31 @@ __global__ __launch_bounds__(256) void k_mvg_fwd(MvgArgs a) {
     for (int u = 0; u < V; ++u) {
       uint32_t c[4] = {(uint32_t)i, (uint32_t)(v0 + u), a.fid, 0u};
       philox(c, keys);
-      box_muller_scaled(u24(c[0]), u24(c[1]), z[u][0], z[u][1]);
-      box_muller_scaled(u24(c[2]), u24(c[3]), z[u][2], z[u][3]);
+      if constexpr (HIT) {
+        box_muller(u24(c[0]), u24(c[1]), z[u][0], z[u][1]);
+        box_muller(u24(c[2]), u24(c[3]), z[u][2], z[u][3]);
+      } else {
+        box_muller_scaled(u24(c[0]), u24(c[1]), z[u][0], z[u][1]);
+        box_muller_scaled(u24(c[2]), u24(c[3]), z[u][2], z[u][3]);
+      }
     }
 #pragma unroll
     for (int u = 0; u < V; ++u) {
       const f32x4 x = stencil_values(s[u], z[u]);
-      const float lo = min4(x), hi = max4(x);
+      float lo = min4(x), hi = max4(x);
       if constexpr (HIT) {
         uint32_t c1[4] = {(uint32_t)i, (uint32_t)(v0 + u), a.fid, 1u};
         philox(c1, keys);
         float z4, z5;
         box_muller(u24(c1[0]), u24(c1[1]), z4, z5);
-        const float t = s[u].L44 * z4;
-        nmin[u] += __popcll(__ballot(on && t < lo));
-        nmax[u] += __popcll(__ballot(on && t > (s[u].first < 4 ? hi : -hi)));
+        const float cm = fmaf(L4[u][3], z[u][3],
+                              fmaf(L4[u][2], z[u][2], fmaf(L4[u][0], z[u][0], L4[u][1] * z[u][1])));
+        const float xv = fmaf(s[u].L44, z4, cm);
+        // no neighbour, or none that is not NaN: +-inf
+        lo = __builtin_fminf(lo, __builtin_inff());
+        hi = __builtin_fmaxf(hi, -__builtin_inff());
+        nmin[u] += __popcll(__ballot(on && xv < lo));
+        nmax[u] += __popcll(__ballot(on && xv > hi));
       } else {
         add(lo * inv[u], on, nmin[u], qmin[u]);
         add(hi * invm[u], on, nmax[u], qmax[u]);
