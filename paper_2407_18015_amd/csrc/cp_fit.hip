@@ -316,14 +316,15 @@ __global__ __launch_bounds__(256) void k_fit_mvg(FitArgs a, double jitter) {
 // Small FP32 grids give the SIMDs a wave or two each, which wait for their
 // members: they fetch them eight at a time with no serial remainder, the
 // smallest as groups of two vertices (twice the waves).  20 members, in us, four
-// vertices by fours / by eights / two by eights:
+// vertices by fours / by eights / two by eights (members in the last-level cache):
 //   Epanechnikov  64^2 5.3 / 4.6 / 3.8, 500^2 (62500 groups of four) 7.4 / 6.0 /
-//     5.0, 600^2 13.6 / 8.0 / 7.0, 720^2 (129600) 12.4 / 7.7 / 8.4, 1000^2 (250000)
-//     16.7 / 13.9 / 14.2, 1200^2 (360000) 19.8 / 20.8 / 21.4, 2048^2 57 / 70 / 70;
+//     5.0, 600^2 13.6 / 8.0 / 7.0, 720^2 (129600) 12.4 / 7.7 / 8.4, 800^2 (160000)
+//     14.2 / 9.7 / 9.7, 1200^2 (360000) 19.8 / 20.8 / 21.4, 2048^2 57 / 70 / 70;
 //   uniform  500^2 5.4 / 5.5 / 4.3, 600^2 7.2 / 6.9 / 6.3, 720^2 8.5 / 7.9 / 8.3,
-//     800^2 (160000) 9.8 / 9.5 / 10.1, 1000^2 12.6 / 13.1 / 13.9.
-// FP64 loses by eights at every size.
-constexpr int64_t kFitSmall = 98304, kFitMid = 262144, kFitMidUniform = 163840;
+//     800^2 9.8 / 9.5 / 10.1, 1000^2 12.6 / 13.1 / 13.9.
+// At 1024^2, members from memory, eights are slower (16.6 against 18.2), as FP64
+// is at every size.
+constexpr int64_t kFitSmall = 98304, kFitMid = 163840;
 
 template <typename T, int MODEL, int V, int U>
 hipError_t launch_fit_vec(const FitArgs& a, hipStream_t st) {
@@ -341,7 +342,7 @@ hipError_t launch_fit(const FitArgs& a, hipStream_t st) {
       const int64_t n = (int64_t)a.H * (a.W / V);
       if constexpr (sizeof(T) == 4) {
         if (n <= kFitSmall) return launch_fit_vec<T, MODEL, 2, 8>(a, st);
-        if (n <= (MODEL == CP_UNIFORM ? kFitMidUniform : kFitMid)) return launch_fit_vec<T, MODEL, 4, 8>(a, st);
+        if (n <= kFitMid) return launch_fit_vec<T, MODEL, 4, 8>(a, st);
       }
       return launch_fit_vec<T, MODEL, V, 0>(a, st);
     }
