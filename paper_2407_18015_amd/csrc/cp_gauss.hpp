@@ -19,10 +19,13 @@
 // of phi and the four Phi((t - d_n) r_n) (or of phi, a density of one
 // neighbour and the other Phi) falls off like exp(-w^2 / (2 V)), V = 1 + sum
 // of r_n^2 over the neighbours that vary inside the window.  With
-// h = 2 pi / sqrt(2 Lam V) the error is about exp(-Lam): below 8e-9 for
-// Lam = 17 (FP32) and 1e-15 for Lam = 32 (FP64) over random stencils with
-// ratios up to e^2, probabilities and derivative integrands alike.  Five
-// equal sigmas take 27 nodes (FP64: 52); fitted fields of 20 members, whose
+// h = 2 pi / sqrt(2 Lam V) it leaves out at most 2 exp(-Lam) of a probability
+// (of the density alone where no neighbour varies in the window, V = 1) and up
+// to 2 Lam times that of a derivative's integrand.  Lam = 19.5 in FP32, 7e-9, and
+// 37.5 in FP64, 1e-16 and 8e-15: over random stencils, narrow vertices beside
+// wide and distant neighbours among them, below the rounding (with 17 and 32,
+// 2e-14 and 8e-13 of FP64 probabilities and derivatives were left out).  Five
+// equal sigmas take 27 nodes (FP64: 53); fitted fields of 20 members, whose
 // sigmas differ by up to a factor of two or three, about 30 to 45.
 // A neighbour much narrower than the vertex makes h small everywhere although
 // the integrand is steep only near d_n.  There the rule is composite
@@ -62,13 +65,13 @@ template <>
 struct GaussRule<float> {
   static constexpr int K = 7, N = 6;
   static constexpr float c[7] = {-6.f, -4.f, -2.f, 0.f, 2.f, 4.f, 6.f};
-  static constexpr double hc = 1.07755;
+  static constexpr double hc = 1.00612;
 };
 template <>
 struct GaussRule<double> {
   static constexpr int K = 11, N = 10;
   static constexpr double c[11] = {-8.5, -6.0, -4.5, -3.0, -1.5, 0.0, 1.5, 3.0, 4.5, 6.0, 8.5};
-  static constexpr double hc = 0.78539816339744830962;
+  static constexpr double hc = 0.72552;
 };
 
 // S = Pr(neighbour above) and F = 1 - S from z's sign and its tail q, by the
@@ -172,7 +175,8 @@ CP_HD void gauss_plan(GaussPlan<T, P>& g, T mv, T sv, const T (&mn)[4], const T 
     for (int n = 0; n < 4; ++n) cuts += g.cuts_inside(n);
     g.panels = !(nodes <= T(N) * cuts);
   }
-  g.m = g.panels ? 0 : (int)(C / g.h);
+  // to the node nearest to C, whose cell reaches at least there
+  g.m = g.panels ? 0 : (int)(C / g.h + T(0.5));
 }
 
 // Visit the nodes of the plan in order: node(position in P, position, weight)
