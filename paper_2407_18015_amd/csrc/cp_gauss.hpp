@@ -84,10 +84,11 @@ CP_HD void gauss_sides(T z, T q, T& S, T& F) {
   S = sel(neg, c, q);
   F = sel(neg, q, c);
 }
-// normal density factor exp(-z^2 / 2) of the scaled deviate zs = z kTailScale
+// normal density factor exp(-t^2 / 2) (scaled after the square, whose rounding
+// is then the only one that the exponential of all neighbours' terms inherits)
 template <typename T>
-CP_HD T gauss_density(T zs) {
-  return exp2_neg(-zs * zs);
+CP_HD T gauss_density(T t) {
+  return exp2_neg(t * t * T(-kTailScale * kTailScale));
 }
 
 // A stencil in vertex units and its rule; P: the type of z_n = (t - d) rs
@@ -180,7 +181,8 @@ CP_HD void gauss_plan(GaussPlan<T, P>& g, T mv, T sv, const T (&mn)[4], const T 
 }
 
 // Visit the nodes of the plan in order: node(position in P, position, weight)
-// for each, flush() after at most N of them and at the end.
+// for each, flush(scale) after at most N of them and at the end: the sums since
+// the last one, times a panel's half-length or the step.
 template <typename T, typename P, typename Node, typename Flush>
 CP_HD void gauss_nodes(const GaussPlan<T, P>& g, Node node, Flush flush) {
   using R = GaussRule<T>;
@@ -210,18 +212,18 @@ CP_HD void gauss_nodes(const GaussPlan<T, P>& g, Node node, Flush flush) {
           const P hl = (P(x1) - P(x0)) * P(0.5);
           tp[u] = cfma(hl, P(GL<N>::x[j + u]), (P(x0) + P(x1)) * P(0.5));
           t[u] = T(tp[u]);
-          w[u] = T(hl) * T(GL<N>::w[j + u]);
+          w[u] = T(GL<N>::w[j + u]);
         } else {
           t[u] = T(i + u) * g.h;
           tp[u] = P(t[u]);
-          w[u] = i + u > g.m ? T(0) : g.h;
+          w[u] = i + u > g.m ? T(0) : T(1);
         }
       }
       i += 2;
       node(tp[0], t[0], w[0]);
       node(tp[1], t[1], w[1]);
     }
-    flush();
+    flush(g.panels ? (P(x1) - P(x0)) * P(0.5) : P(g.h));
     x0 = x1;
     if (g.panels ? !(x1 < C) : i > g.m) break;
   }
@@ -234,7 +236,9 @@ template <typename T>
 CP_HD void gauss_vertex(T mv, T sv, const T (&mn)[4], const T (&sn)[4], const bool (&pres)[4], T (&out)[4]) {
   GaussPlan<T, T> g;
   gauss_plan(g, mv, sv, mn, sn, pres);
-  T acc[4] = {T(0), T(0), T(0), T(0)};
+  // sums of N nodes, and of those (one sum of 200 nodes in FP32 reached 9e-7 of
+  // the 1e-6 that the probabilities may be off)
+  T acc[4] = {T(0), T(0), T(0), T(0)}, sum[4] = {T(0), T(0), T(0), T(0)};
   const T slope = vconst(T(kTailSlope));
   const auto node = [&](T, T t, T w) {
     T S[4], F[4];
@@ -246,14 +250,20 @@ CP_HD void gauss_vertex(T mv, T sv, const T (&mn)[4], const T (&sn)[4], const bo
       gauss_sides(z, q, S[n], F[n]);
     }
     // e, w (n = 0, 2) take S in t1 and F in t2; n, s the reverse
-    const T phi = w * gauss_density(t * T(kTailScale));
+    const T phi = w * gauss_density(t);
     const T sa = phi * (S[0] * S[2]), fa = phi * (F[0] * F[2]), sb = S[1] * S[3], fb = F[1] * F[3];
-    acc[0] = cfma(sa, sb, acc[0]);
-    acc[1] = cfma(fa, fb, acc[1]);
-    acc[2] = cfma(sa, fb, acc[2]);
-    acc[3] = cfma(fa, sb, acc[3]);
+    sum[0] = cfma(sa, sb, sum[0]);
+    sum[1] = cfma(fa, fb, sum[1]);
+    sum[2] = cfma(sa, fb, sum[2]);
+    sum[3] = cfma(fa, sb, sum[3]);
   };
-  gauss_nodes(g, node, [] {});
+  gauss_nodes(g, node, [&](T scale) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc[q] = cfma(sum[q], scale, acc[q]);
+      sum[q] = T(0);
+    }
+  });
   T scale = T(0.39894228040143267794);  // 1 / sqrt(2 pi)
 #pragma unroll
   for (int n = 0; n < 4; ++n) scale *= pres[n] ? T(1) : T(2);
@@ -296,7 +306,7 @@ CP_HD void gauss_vertex_jac(T mv, T sv, const T (&mn)[4], const T (&sn)[4], cons
   // FP32: z_n as one FP64 FMA (d_n rs_n rounds far below z_n's own FP32)
   const P nd[4] = {-g.d[0] * g.rs[0], -g.d[1] * g.rs[1], -g.d[2] * g.rs[2], -g.d[3] * g.rs[3]};
   const auto node = [&](P tp, T t, T w) {
-    const T phi = w * gauss_density(t * T(kTailScale));
+    const T phi = w * gauss_density(t);
     T S[4], F[4], z[4], e[4];
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
@@ -318,11 +328,11 @@ CP_HD void gauss_vertex_jac(T mv, T sv, const T (&mn)[4], const T (&sn)[4], cons
       qb[n] = cfma(v, z[n], qb[n]);
     }
   };
-  const auto flush = [&] {
+  const auto flush = [&](P scale) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      a[n] += P(qa[n]);
-      b[n] += P(qb[n]);
+      a[n] = cfma(P(qa[n]), scale, a[n]);
+      b[n] = cfma(P(qb[n]), scale, b[n]);
       qa[n] = qb[n] = T(0);
     }
   };

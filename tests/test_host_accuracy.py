@@ -72,3 +72,17 @@ def test_gaussian_derivatives_fp64(evaluate, spread):
     o = evaluate("gauss", weighted(stencils(5, 600, spread, 0.0, F64), 6), F64)
     exact = o[:, 18:]
     assert (np.abs(o[:, 4:14] - exact) / np.abs(exact).max(1, keepdims=True)).max() <= 1e-14
+
+
+# FP32, narrow neighbours one to four deviations above the vertex: P_min is near 1,
+# a sum of 100 to 200 nodes.  Half the parity bound of 1e-6 is left to the sum and
+# the tails; the other half belongs to the hardware's reciprocal and exponential.
+def test_gaussian_sums_fp32(evaluate):
+    rng = np.random.default_rng(7)
+    n = 2500
+    w = 0.05 * np.exp(rng.uniform(-3, -1, (n, 5)))
+    c = 0.3 + 0.05 * rng.uniform(1, 4, (n, 5))
+    w[:, 0], c[:, 0] = 0.05, 0.3
+    p = np.stack([c, w], 2).reshape(n, 10).astype(np.float32).astype(np.float64)
+    o = evaluate("gauss", weighted(p, 8), F32)
+    assert np.abs(o[:, :4] - o[:, 14:18]).max() <= 5e-7
