@@ -96,34 +96,36 @@ __host__ __device__ __forceinline__ double exp2_neg(double y) {
   return __builtin_ldexp(__builtin_fma(f, p, 1.0), (int)n);
 }
 
-// FP64, from the same zs: q = e p8(x) / p9(x) with x = |zs|, the ratio
-// interpolating exp(z^2 / 2) Pr(N(0, 1) > z) at Chebyshev points of (z - 3 sqrt 2)
-// / (z + 3 sqrt 2) over z <= 9.9 (3e-17; 1e-10 at z = 28, where q is 1e-173).
-// All coefficients are positive, so both polynomials lose no digits.  Half the
-// work of erfc and exp, which evaluate every range of z that a wave holds and
-// the exponential twice.
+// FP64, from the same zs: q = e p9(x) / p10(x) with x = |zs|, the ratio
+// interpolating exp(z^2 / 2) Pr(N(0, 1) > z) at Chebyshev points of (z - 4) /
+// (z + 4) over z <= 30 (9e-17 there, 6e-15 at 38, where q vanishes; one degree
+// less reaches 3e-17 up to 9.9, but 1e-10 at 28).  All coefficients are
+// positive, so both polynomials lose no digits.  Half the work of erfc and exp,
+// which evaluate every range of z that a wave holds and the exponential twice.
 __host__ __device__ __forceinline__ void upper_tail(double zs, double, double& q, double& e) {
   double x = __builtin_fabs(zs);
   x = x > 33.0 ? 33.0 : x;  // 2^-x^2 is 0 from here on
   e = exp2_neg(-x * x);
-  double n = 1.6082765204010446e-05;
-  n = __builtin_fma(n, x, 0.00034988923535707203);
-  n = __builtin_fma(n, x, 0.003639910750331352);
-  n = __builtin_fma(n, x, 0.02342658443092272);
-  n = __builtin_fma(n, x, 0.10161629013929727);
-  n = __builtin_fma(n, x, 0.30430775035359225);
-  n = __builtin_fma(n, x, 0.6177961374727721);
-  n = __builtin_fma(n, x, 0.7876151126824155);
+  double n = 5.4831700515742165e-06;
+  n = __builtin_fma(n, x, 0.00012723838728142183);
+  n = __builtin_fma(n, x, 0.0014414748868951692);
+  n = __builtin_fma(n, x, 0.010325276039219889);
+  n = __builtin_fma(n, x, 0.051173036386345586);
+  n = __builtin_fma(n, x, 0.18141961556916425);
+  n = __builtin_fma(n, x, 0.4602520793420452);
+  n = __builtin_fma(n, x, 0.8092325515282937);
+  n = __builtin_fma(n, x, 0.9039577837722884);
   n = __builtin_fma(n, x, 0.5);
-  double d = 4.746553494444576e-05;
-  d = __builtin_fma(d, x, 0.0010326383725138887);
-  d = __builtin_fma(d, x, 0.010776812870550278);
-  d = __builtin_fma(d, x, 0.06988448654069497);
-  d = __builtin_fma(d, x, 0.3076023397021155);
-  d = __builtin_fma(d, x, 0.9469179733868519);
-  d = __builtin_fma(d, x, 2.0285868500055297);
-  d = __builtin_fma(d, x, 2.9048174912382168);
-  d = __builtin_fma(d, x, 2.5146675040644864);
+  double d = 1.6182640174000773e-05;
+  d = __builtin_fma(d, x, 0.00037552237450265343);
+  d = __builtin_fma(d, x, 0.004265940310335866);
+  d = __builtin_fma(d, x, 0.03074417129493282);
+  d = __builtin_fma(d, x, 0.15408044501589319);
+  d = __builtin_fma(d, x, 0.5570200103834194);
+  d = __builtin_fma(d, x, 1.4629334901909385);
+  d = __builtin_fma(d, x, 2.7442300072908297);
+  d = __builtin_fma(d, x, 3.506283604000219);
+  d = __builtin_fma(d, x, 2.7473528462442243);
   d = __builtin_fma(d, x, 1.0);
 #if defined(__HIP_DEVICE_COMPILE__)
   // reciprocal to 2^-24, one Newton step, and the quotient corrected by its remainder

@@ -86,3 +86,12 @@ def test_gaussian_sums_fp32(evaluate):
     p = np.stack([c, w], 2).reshape(n, 10).astype(np.float32).astype(np.float64)
     o = evaluate("gauss", weighted(p, 8), F32)
     assert np.abs(o[:, :4] - o[:, 14:18]).max() <= 5e-7
+
+
+# FP64 tails at every argument: zs = kTailScale z and zs^2 round to 2^-53 each, which
+# the exponential turns into z^2 (1 + 1/2) 2^-53 of q, the constant's own rounding
+# adds another z^2 2^-53, and 16 units cover the ratio of the polynomials.
+def test_tails_fp64(evaluate):
+    z = np.linspace(-30.0, 30.0, 6001)[:, None]
+    err = np.abs(evaluate("tail", z)[:, 0])
+    assert np.all(err <= (2.5 * z[:, 0] ** 2 + 16) * 2.0**-53)
