@@ -15,8 +15,8 @@
 //        first and the F that ends last;
 //   4th: both S and the F that ends last;
 //   5th: both S (every F has ended).
-// The factors that can vary are evaluated clamped to [0, 1] (a modifier, no
-// instruction), the others are 1, so every piece is integrated exactly by the
+// The factors that can vary are evaluated with their arguments clamped, the
+// others are 1, so every piece is integrated exactly by the
 // rule of its own degree: two to three factors instead of four, and for the
 // Epanechnikov model 4, 6, 4, 6, 4 nodes beside the centre instead of 5 x 7.
 //
@@ -31,9 +31,11 @@
 
 namespace cp {
 
-// A factor by its argument: uniform F = (x - x0) i, S = 1 - that with
-// (x0, i) = (a, 1/L); Epanechnikov v = (u + 1) / 2 = (x - x0) i with
-// (x0, i) = (d - w, 1/(2 w)).  In both F rises from 0 to 1 on v in [0, 1].
+// A factor of a term by its argument v = (x - x0) i.  Uniform: v clamped to
+// [0, 1], for S (x0, i) = (b, -1/L), for F (a, 1/L).  Epanechnikov: (v^3 - 3 v +
+// 2) / 4 of v clamped to [-1, 1], for S (d, 1/w), for F (d, -1/w).  The origins
+// are the parameters' own differences: a start point d - w rounds, which every
+// factor of the pieces beside it would inherit.
 template <typename T>
 struct Ramp {
   T x0, i;
@@ -58,20 +60,24 @@ struct MixedNodes {
   }
 };
 
-// Integral over the half-length hl around mid of the vertex kernel (uniform 1,
-// Epanechnikov 1 - t^2) times NS survival and NF distribution factors, by the
-// N-point rule, REM: plus its remainder.  A factor's argument is clamped on the
-// whole piece or nowhere inside it (its clamp points are events), so the
-// midpoint decides whether it has a leading term.
-template <typename T, int MODEL, int NS, int NF, int N, bool REM>
-CP_HD T mixed_piece(const MixedNodes<T>& nodes, T iwv, T l, T r, const Ramp<T> (&s)[NS > 0 ? NS : 1], const Ramp<T> (&f)[NF > 0 ? NF : 1]) {
+// acc plus the integral over [l, r] of the vertex kernel (uniform 1,
+// Epanechnikov 1 - t^2) times K factors, by the N-point rule, REM: plus its
+// remainder.  A factor's argument is clamped on the whole piece or nowhere
+// inside it (its clamp points are events), so the midpoint decides whether it
+// has a leading term.
+//
+// Epanechnikov: the Horner form of v^3 - 3 v + 2 with a clamp of its own (a half
+// rate instruction).  From t = (v + 1) / 2, whose clamp is a modifier, as 1/2 -
+// t^2 (3/2 - t), the terms' error is a quarter to a third larger (rms 6.1e-9
+// against 4.8e-9 in FP32, widths within a factor of four).
+template <typename T, int MODEL, int K, int N, bool REM>
+CP_HD T mixed_piece(const MixedNodes<T>& nodes, T iwv, T l, T r, const Ramp<T> (&f)[K], T acc) {
   const T mid = (l + r) * T(0.5), hl = (r - l) * T(0.5);
-  T am[NS + NF], bm[NS + NF];
+  T am[K], bm[K];
 #pragma unroll
-  for (int i = 0; i < NS + NF; ++i) {
-    const Ramp<T>& q = i < NS ? s[i < NS ? i : 0] : f[i < NS ? 0 : i - NS];
-    am[i] = (mid - q.x0) * q.i;
-    bm[i] = hl * q.i;
+  for (int i = 0; i < K; ++i) {
+    am[i] = (mid - f[i].x0) * f[i].i;
+    bm[i] = hl * f[i].i;
   }
   const T av = mid * iwv, bv = hl * iwv;
   T sum = T(0);
@@ -86,30 +92,23 @@ CP_HD T mixed_piece(const MixedNodes<T>& nodes, T iwv, T l, T r, const Ramp<T> (
       prod = cfma(-t, t, T(1));
     }
 #pragma unroll
-    for (int i = 0; i < NS + NF; ++i) {
-      const T v = clamp01(cfma(bm[i], x, am[i]));
-      if constexpr (MODEL == CP_UNIFORM) {
-        prod *= i < NS ? T(1) - v : v;
-      } else {  // F = v^2 (3 - 2 v), halved: its constants are free operands
-        const T v2 = v * v, g = T(1.5) - v;
-        prod *= i < NS ? cfma(-v2, g, T(0.5)) : v2 * g;
-      }
+    for (int i = 0; i < K; ++i) {
+      const T v = cfma(bm[i], x, am[i]);
+      prod *= MODEL == CP_UNIFORM ? clamp01(v) : epa_s4(clamp_nn(v, T(-1), T(1)));
     }
     sum = cfma(T(GL<N>::w[j]), prod, sum);
   }
   if constexpr (REM) {
-    // leading coefficients: S -b (uniform) or b^3 (halved), F the negative,
-    // the vertex's kernel -bv^2 (Epanechnikov)
+    // leading coefficients: b (uniform), b^3, the vertex's kernel -bv^2
     T c = MODEL == CP_UNIFORM ? T(1) : -bv * bv;
 #pragma unroll
-    for (int i = 0; i < NS + NF; ++i) {
-      const T b = MODEL == CP_UNIFORM ? -bm[i] : bm[i] * bm[i] * bm[i];
-      const T m = fabs(am[i] - T(0.5)) < T(0.5) ? b : T(0);
-      c *= i < NS ? m : -m;
+    for (int i = 0; i < K; ++i) {
+      const bool in = MODEL == CP_UNIFORM ? fabs(am[i] - T(0.5)) < T(0.5) : fabs(am[i]) < T(1);
+      c *= in ? (MODEL == CP_UNIFORM ? bm[i] : bm[i] * bm[i] * bm[i]) : T(0);
     }
     sum = cfma(T(GLRem<N>::e), c, sum);
   }
-  return sum * (MODEL == CP_UNIFORM ? hl : T(1 << (NS + NF)) * hl);
+  return cfma(sum, MODEL == CP_UNIFORM ? hl : T(1.0 / (1 << 2 * K)) * hl, acc);
 }
 
 // One saddle term without the centre, times the vertex's width (uniform Lv,
@@ -123,17 +122,17 @@ CP_HD T saddle_term(const MixedNodes<T>& nodes, T iwv, T v0, T v1, const Ramp<T>
   if (!(lo < hi)) return T(0);
   const T s0 = clamp_nn(ss[0], lo, hi), s1 = clamp_nn(ss[1], lo, hi);
   const T f0 = clamp_nn(fe[0], lo, hi), f1 = clamp_nn(fe[1], lo, hi);
-  const Ramp<T> first[1] = {sel(less_mask(ss[1], ss[0]), s[1], s[0])};
-  const Ramp<T> last[1] = {sel(less_mask(fe[0], fe[1]), f[1], f[0])};
+  const Ramp<T> first = sel(less_mask(ss[1], ss[0]), s[1], s[0]);
+  const Ramp<T> last = sel(less_mask(fe[0], fe[1]), f[1], f[0]);
   const T sa = fmin_nn(s0, s1), sb = fmax_nn(s0, s1), fa = fmin_nn(f0, f1), fb = fmax_nn(f0, f1);
   const T p = fmax_nn(sa, fa), q = fmin_nn(sb, fb);
   const T c0 = fmin_nn(sa, fa), c1 = fmin_nn(p, q), c2 = fmax_nn(p, q), c3 = fmax_nn(sb, fb);
-  const Ramp<T> none[1] = {first[0]};
-  T acc = mixed_piece<T, MODEL, 0, 2, U ? 1 : 4, true>(nodes, iwv, lo, c0, none, f);
-  acc += mixed_piece<T, MODEL, 1, 2, U ? 2 : 6, false>(nodes, iwv, c0, c1, first, f);
-  if (!centre) acc += mixed_piece<T, MODEL, 1, 1, U ? 1 : 4, true>(nodes, iwv, c1, c2, first, last);
-  acc += mixed_piece<T, MODEL, 2, 1, U ? 2 : 6, false>(nodes, iwv, c2, c3, s, last);
-  acc += mixed_piece<T, MODEL, 2, 0, U ? 1 : 4, true>(nodes, iwv, c3, hi, s, none);
+  const Ramp<T> sff[3] = {first, f[0], f[1]}, sf[2] = {first, last}, ssf[3] = {s[0], s[1], last};
+  T acc = mixed_piece<T, MODEL, 2, U ? 1 : 4, true>(nodes, iwv, lo, c0, f, T(0));
+  acc = mixed_piece<T, MODEL, 3, U ? 2 : 6, false>(nodes, iwv, c0, c1, sff, acc);
+  if (!centre) acc = mixed_piece<T, MODEL, 2, U ? 1 : 4, true>(nodes, iwv, c1, c2, sf, acc);
+  acc = mixed_piece<T, MODEL, 3, U ? 2 : 6, false>(nodes, iwv, c2, c3, ssf, acc);
+  acc = mixed_piece<T, MODEL, 2, U ? 1 : 4, true>(nodes, iwv, c3, hi, s, acc);
   return acc;
 }
 
@@ -142,7 +141,7 @@ CP_HD T saddle_term(const MixedNodes<T>& nodes, T iwv, T v0, T v1, const Ramp<T>
 template <typename T, int MODEL, bool MM>
 CP_HD void vertex_classes_ue(T p0, T p1, const T (&q0)[4], const T (&q1)[4], const bool (&pres)[4], T& pmin, T& pmax,
                              T& t1, T& t2) {
-  Ramp<T> r[4];
+  Ramp<T> S[4], F[4];
   T st[4], en[4], o[4], v0, v1, k, iwv;
   bool centre;
   if constexpr (MODEL == CP_UNIFORM) {
@@ -161,7 +160,8 @@ CP_HD void vertex_classes_ue(T p0, T p1, const T (&q0)[4], const T (&q1)[4], con
     k = iwv = s.iLv;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      r[i] = {s.a[i], s.iL[i]};
+      S[i] = {s.b[i], -s.iL[i]};
+      F[i] = {s.a[i], s.iL[i]};
       st[i] = s.a[i];
       en[i] = s.b[i];
     }
@@ -184,16 +184,17 @@ CP_HD void vertex_classes_ue(T p0, T p1, const T (&q0)[4], const T (&q1)[4], con
     for (int i = 0; i < 4; ++i) {
       st[i] = s.d[i] - s.w[i];
       en[i] = s.d[i] + s.w[i];
-      r[i] = {st[i], T(0.5) * s.iw[i]};
+      S[i] = {s.d[i], s.iw[i]};
+      F[i] = {s.d[i], -s.iw[i]};
     }
   }
   t1 = t2 = T(0);
   if (!(pres[0] && pres[1] && pres[2] && pres[3])) return;
   const MixedNodes<T> nodes;
-  const Ramp<T> ew[2] = {r[0], r[2]}, ns[2] = {r[1], r[3]};
+  const Ramp<T> ewS[2] = {S[0], S[2]}, ewF[2] = {F[0], F[2]}, nsS[2] = {S[1], S[3]}, nsF[2] = {F[1], F[3]};
   const T ews[2] = {st[0], st[2]}, ewe[2] = {en[0], en[2]}, nss[2] = {st[1], st[3]}, nse[2] = {en[1], en[3]};
-  t1 = cfma(k, saddle_term<T, MODEL>(nodes, iwv, v0, v1, ew, ews, ewe, ns, nss, nse, centre), o[2]);
-  t2 = cfma(k, saddle_term<T, MODEL>(nodes, iwv, v0, v1, ns, nss, nse, ew, ews, ewe, centre), o[3]);
+  t1 = cfma(k, saddle_term<T, MODEL>(nodes, iwv, v0, v1, ewS, ews, ewe, nsF, nss, nse, centre), o[2]);
+  t2 = cfma(k, saddle_term<T, MODEL>(nodes, iwv, v0, v1, nsS, nss, nse, ewF, ews, ewe, centre), o[3]);
 }
 
 }  // namespace cp
