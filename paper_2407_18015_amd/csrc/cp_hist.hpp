@@ -163,11 +163,13 @@ CP_HD void suf_cursor_step(SufCursor<T>& c, int E, T big) {
   c.nxt = past ? big : cfma(c.k, c.d, c.hi);
 }
 
-// The vertex's own bins over [0, hv]: the upper edge nv = hv + k dv of the
-// current bin (k = -(h - 1) .. 0), U there (at p), the bin's density.
+// The vertex's own bins over [0, hv]: the upper edge nv = k dv of the current
+// bin (k = 1 .. h; hv itself for the last: counted up, as P_min weighs the edges
+// near 0 and there are at most h of them), U there (at p), the bin's density.
 template <typename T>
 struct VertexBins {
   const T* p;
+  int left;  // bins above the current one
   T k, nv, pv, uv, dv, idv;
 };
 
@@ -177,21 +179,23 @@ CP_HD void vertex_bins_init(VertexBins<T>& b, const HistSuf<T>& L, int ev, T hv)
   b.dv = hv * (T(1) / T(h));
   b.idv = T(h) * crcp(hv);
   b.p = L.base + 3 * L.E + ev;
-  b.k = T(1 - h);
+  b.k = T(1);
+  b.left = h - 1;
   b.nv = h > 1 ? b.dv : hv;
   b.uv = *b.p;
   b.pv = (L.U(ev, 0) - b.uv) * b.idv;
 }
 
-// (past the last bin, k = 1, the sweep has ended)
+// (past the last bin the sweep has ended)
 template <typename T>
 CP_HD void vertex_bins_step(VertexBins<T>& b, int E, T hv) {
-  b.p += b.k < T(0) ? E : 0;
+  b.p += b.left > 0 ? E : 0;
+  b.left -= 1;
   b.k += T(1);
   const T u = *b.p;
   b.pv = (b.uv - u) * b.idv;
   b.uv = u;
-  b.nv = cfma(tmin(b.k, T(0)), b.dv, hv);
+  b.nv = b.left > 0 ? b.k * b.dv : hv;
 }
 
 // P_min and P_max of vertex ev; neighbour ranges [lo_i, hi_i] in the vertex
@@ -218,6 +222,18 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
 #pragma unroll
   for (int i = 0; i < 4; ++i) suf_cursor_init(c[i], L, en[i], lo[i], hi[i], pres[i], big);
   T x0 = T(0), amin = T(0), amax = T(0), a1 = T(0), a2 = T(0);
+  // integrals over the vertex's open bin, whose density they get when it ends
+  T bmin = T(0), bmax = T(0), b1 = T(0), b2 = T(0);
+  const auto fold = [&] {
+    amin = cfma(vb.pv, bmin, amin);
+    amax = cfma(vb.pv, bmax, amax);
+    bmin = bmax = T(0);
+    if constexpr (SAD) {
+      a1 = cfma(vb.pv, b1, a1);
+      a2 = cfma(vb.pv, b2, a2);
+      b1 = b2 = T(0);
+    }
+  };
   const int maxit = 5 * (h + 1) + 2;  // every step crosses at least one edge
   for (int it = 0; it < maxit; ++it) {
     if (!(x0 < hv)) break;
@@ -234,11 +250,17 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
     // to at most six times the result.  27 operations for P_min and P_max
     // (39 with the saddle terms) against 46 (92) from the end values in
     // Bernstein form.
-    const T mid = (x0 + x1) * T(0.5), hl = (x1 - x0) * T(0.5);
+    // The midpoint is reached from the interval's end, whose distance to the
+    // cursor's edge is exact or small, and an interval's integrals get the
+    // vertex's density with its whole bin: with a rounded midpoint and one sum
+    // over all intervals the probabilities rounded worse than the end values'
+    // (rms, FP32 and 4 bins 1.13 times, FP64 and 10 bins 1.1; so 1.04 and 0.9;
+    // it costs 1% of the sweep).
+    const T hl = (x1 - x0) * T(0.5);
     T S[4], F[4], t[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      S[i] = cfma(c[i].slope, c[i].nxt - mid, c[i].snx);
+      S[i] = cfma(c[i].slope, (c[i].nxt - x1) + hl, c[i].snx);
       F[i] = c[i].tot - S[i];
       t[i] = c[i].slope * hl;
     }
@@ -251,28 +273,32 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
       f1[p] = cfma(F[p], t[p + 2], F[p + 2] * t[p]);
       q2[p] = t[p] * t[p + 2];
     }
-    const T top = T(0.2) * (q2[0] * q2[1]), wgt = vb.pv * (x1 - x0);
+    const T top = T(0.2) * (q2[0] * q2[1]), wgt = x1 - x0;
     const auto quartic = [&](T p0, T p1, T r0, T r1) {  // p1 r1 with the sign of its term
       const T m = cfma(p0, q2[1], cfma(q2[0], r0, p1 * r1));
       return cfma(T(1.0 / 3.0), m, cfma(p0, r0, top));
     };
-    amin = cfma(wgt, quartic(s0[0], s1[0], s0[1], s1[1]), amin);
-    amax = cfma(wgt, quartic(f0[0], f1[0], f0[1], f1[1]), amax);
+    bmin = cfma(wgt, quartic(s0[0], s1[0], s0[1], s1[1]), bmin);
+    bmax = cfma(wgt, quartic(f0[0], f1[0], f0[1], f1[1]), bmax);
     if constexpr (SAD) {
-      a1 = cfma(wgt, quartic(s0[0], s1[0], f0[1], -f1[1]), a1);
-      a2 = cfma(wgt, quartic(f0[0], f1[0], s0[1], -s1[1]), a2);
-      settle(a1);
-      settle(a2);
+      b1 = cfma(wgt, quartic(s0[0], s1[0], f0[1], -f1[1]), b1);
+      b2 = cfma(wgt, quartic(f0[0], f1[0], s0[1], -s1[1]), b2);
+      settle(b1);
+      settle(b2);
     }
     // the old state is dead from here on: the steps update it in place
-    settle(amin);
-    settle(amax);
+    settle(bmin);
+    settle(bmax);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (c[i].nxt == x1) suf_cursor_step(c[i], L.E, big);
-    if (vb.nv == x1) vertex_bins_step(vb, L.E, hv);
+    if (vb.nv == x1) {
+      fold();
+      vertex_bins_step(vb, L.E, hv);
+    }
     x0 = x1;
   }
+  fold();
   pmin = amin;
   pmax = amax;
   t1 = a1;

@@ -162,7 +162,7 @@ __host__ __device__ void hist_jac_both(const HistSuf<T>& L, int ev, const int (&
     x0 = x1;
   }
   // remaining vertex bins (the sweep ended inside or past them): no range
-  for (int k = (int)vb.k + h - 1; k < h; ++k) {
+  for (int k = (int)vb.k - 1; k < h; ++k) {
     J.put(0, jv, (gmin * vS + gmax * vF) * vb.idv);
     J.step(0, jv);
     amin = cfma(vb.pv, vS, amin);
