@@ -39,9 +39,11 @@ __device__ __forceinline__ void class_store(const ClassPtrs<T>& f, int y, int x,
   if (f.preg) f.preg[at] = T(1) - pmin - pmax - ps;
 }
 
-// 64 x TY vertices per block of NT threads (TY / (NT / 64) rows per thread)
+// 64 x TY vertices per block of NT threads (TY / (NT / 64) rows per thread).
+// Four waves per SIMD asked for where the registers stop one short of them.
 template <typename T, int MODEL, int TY, int NT>
-__global__ __launch_bounds__(NT) void k_classify_ue(ClassPtrs<T> f, int tiles_x, int ntiles) {
+__global__ __launch_bounds__(NT, MODEL == CP_EPANECHNIKOV && sizeof(T) == 8 ? 4 : 1) void k_classify_ue(
+    ClassPtrs<T> f, int tiles_x, int ntiles) {
   constexpr int TX = kFwdTX, EX = TX + 2, EY = TY + 2, E = EX * EY;
   static_assert(NT % TX == 0 && TY % (NT / TX) == 0, "rows must split evenly over the threads");
   __shared__ T lds[2 * E];

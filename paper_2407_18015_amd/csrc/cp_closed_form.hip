@@ -30,8 +30,10 @@ __global__ __launch_bounds__(kFwdTX* TY) void k_fwd_hist(FieldPtrs<T> f, int til
 // ---------------------------------------------------------------------------
 // adjoint
 // ---------------------------------------------------------------------------
+// (four waves per SIMD asked for where the registers stop one short of them)
 template <typename T, int MODEL, int OX, int OY>
-__global__ __launch_bounds__(256) void k_bwd_ue(FieldPtrs<T> f, int tiles_x, int ntiles) {
+__global__ __launch_bounds__(256, MODEL == CP_GAUSSIAN && sizeof(T) == 4 ? 4 : 1) void k_bwd_ue(
+    FieldPtrs<T> f, int tiles_x, int ntiles) {
   __shared__ T lds[bwd_ue_lds_elems<OX, OY>()];
   const int t = xcd_tile(blockIdx.x, ntiles);
   tile_bwd_ue<T, MODEL, OX, OY, 256>(f, (t / tiles_x) * OY, (t % tiles_x) * OX, lds, threadIdx.x);
