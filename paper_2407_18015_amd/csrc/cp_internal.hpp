@@ -17,6 +17,9 @@ constexpr int kMaxBins = 32;
 // entries of the five stencil slots per bin, then one tail per neighbour
 __host__ __device__ constexpr int64_t hist_ws_planes(int h) { return 5 * (int64_t)h + 4; }
 
+// Philox blocks of four samples (the sum of a count near 2^31 and 3 overflows)
+__host__ __device__ constexpr int semi_blocks(int ns) { return (ns >> 2) + ((ns & 3) != 0); }
+
 // A validated field description (row_stride resolved).
 struct Field {
   int H = 0, W = 0;

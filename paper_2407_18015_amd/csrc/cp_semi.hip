@@ -312,7 +312,7 @@ __global__ __launch_bounds__(256, 5) void k_semi(SemiArgs<T> a, int tiles_x, int
         }
       };
       // (the pass that holds a partial block looks at every sample)
-      const int blocks = (a.ns + 3) >> 2, full = a.ns & 3 ? (blocks - 1) & ~63 : blocks;
+      const int blocks = semi_blocks(a.ns), full = a.ns & 3 ? (blocks - 1) & ~63 : blocks;
       for (int b = lane; b < full; b += 64) block(b, std::true_type{});
       if (full + lane < blocks) block(full + lane, std::false_type{});
       // the tables are read before the next vertex overwrites them

@@ -1,0 +1,37 @@
+"""Dispatch rules of the library on the CPU (tests/helpers/host_rules.cpp, a
+host-only build of its headers)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = os.path.join(ROOT, "tests", "helpers", "host_rules.cpp")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    clang = "/opt/rocm/llvm/bin/clang++"
+    if not (os.path.exists(hipcc) and os.path.exists(clang)):
+        pytest.skip("no HIP compiler")
+    d = tmp_path_factory.mktemp("host_rules")
+    obj, exe = str(d / "host_rules.o"), str(d / "host_rules")
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2407_18015_amd", "csrc")]
+    subprocess.run([hipcc, "-xhip", "--offload-host-only", "-O1", "-std=c++17", *inc, "-c", SRC, "-o", obj],
+                   check=True)
+    subprocess.run([clang, obj, "-o", exe], check=True)
+
+    def call(*args):
+        r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return r.stdout.split()
+
+    return call
+
+
+# every sample count that the entry point takes, to the last of 31 bits
+@pytest.mark.parametrize("ns", [1, 3, 4, 5, 1000, 2**31 - 5, 2**31 - 4, 2**31 - 3, 2**31 - 1])
+def test_semianalytical_blocks(rules, ns):
+    assert int(rules("blocks", ns)[0]) == (ns + 3) // 4
