@@ -20,6 +20,25 @@ __host__ __device__ constexpr int64_t hist_ws_planes(int h) { return 5 * (int64_
 // Philox blocks of four samples (the sum of a count near 2^31 and 3 overflows)
 __host__ __device__ constexpr int semi_blocks(int ns) { return (ns >> 2) + ((ns & 3) != 0); }
 
+// Whether the semianalytical estimator gives a vertex to a thread, which loops
+// over its samples, or to a wave, whose passes take 256 of them (so that its time
+// is the same from a few samples to 256).  The two cross where a wave's pass costs
+// as much as the loop, in samples at 256^2 / 512^2 / 1024^2 / 2048^2:
+//   FP32   1 bin 69 / 139 / 166 / 175, 4 bins 53 / 123 / 151 / 162, 10 bins 55 /
+//     123 / 150 / 160, 16 bins 46 / 113 / 126 / 137, 24 bins 46 / 80 / 94 / 100,
+//     32 bins 43 / 68 / 65 / 67;
+//   FP64   4 bins 66 / 135 / 162 / 174, 10 bins - / 137 / 144 / 152, 16 bins - / 82
+//     / 78 / 80, 32 bins - / 46 / 48 / -
+// (1024^2, ten bins, 128 samples: 721 us by thread, 828 by wave; 256: 1409 and
+// 828).  From 16 (FP64 12) bins on the staged masses leave the loop ever fewer
+// waves; fields of less than 800 thousand vertices leave some of the CUs' waves
+// unused, and small ones leave the loop waiting on its own latencies, 1.1 us a
+// sample, for longer than a wave's 0.8 ns a vertex (but for one block of four).
+__host__ __device__ constexpr bool semi_by_thread(int ns, int h, size_t el, int64_t vertices) {
+  return ns <= 168 - 2 * h - (vertices < 3 << 18 ? 30 : 0) && ns * h <= (el == 4 ? 2300 : 1350) &&
+         (ns <= 4 || ns * 1350 <= vertices);
+}
+
 // A validated field description (row_stride resolved).
 struct Field {
   int H = 0, W = 0;

@@ -382,13 +382,7 @@ hipError_t semi_typed(const Field& f, const void* params, void* pmin, void* pmax
   a.k0 = (uint32_t)f.seed;
   a.k1 = (uint32_t)(f.seed >> 32);
   a.fid = f.fid;
-  // A wave's tables cost as much as about 100 samples of the thread-per-vertex
-  // loop, whose samples get dearer with the bins.  1024^2, ten bins: 64 samples
-  // 404 us by thread and 851 by wave, 128: 739 and 850, 256: 1438 and 857;
-  // 512^2, 32 bins in FP64: 64 samples 533 and 376.  Small fields leave the
-  // thread loop waiting on its own latencies, about 1.1 us a sample against
-  // 0.8 ns a vertex (40^2 x 1000: 1086 us by thread and 30 by wave).
-  if (f.ns < 128 && f.ns * (f.nb + 6) < 2048 && f.ns * 1350 <= (int64_t)f.H * f.W) {
+  if (semi_by_thread(f.ns, f.nb, sizeof(T), (int64_t)f.H * f.W)) {
     // tile height: the staged planes (the masses overwritten by their
     // cumulative sums) must fit the LDS
     const size_t per_row = sizeof(T) * (size_t)(2 + f.nb) * (kFwdTX + 2);
