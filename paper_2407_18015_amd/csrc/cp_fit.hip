@@ -31,37 +31,6 @@ namespace {
 
 constexpr int kFitTX = 64, kFitTY = 4, kMaxRegMembers = 32;
 
-// Bin of a member x of a vertex's range [lo, hi]: floor((x - lo) / (hi - lo) * nb),
-// clamped.  The quotient is correctly rounded; all members share the divisor,
-// so it is its rounded reciprocal's product, corrected twice by the exact
-// remainder (Markstein's scheme, as div_count), five operations.  A remainder
-// that underflows then belongs to a quotient below 2^-24: bin 0 either way.
-// Ranges outside the limits, infinite and NaN ones divide.
-template <typename T>
-struct BinOf {
-  T lo, range, inv, fnb;
-  int nb;
-  bool exact;
-  __device__ __forceinline__ BinOf(T lo_, T hi, int nb_) : lo(lo_), range(rn_sub(hi, lo_)), fnb(T(nb_)), nb(nb_) {
-    constexpr T kLo = sizeof(T) == 8 ? T(1e-200) : T(1e-30f), kHi = sizeof(T) == 8 ? T(1e200) : T(1e30f);
-    exact = range >= kLo && range <= kHi;
-    inv = rn_div(T(1), range);
-  }
-  __device__ __forceinline__ int operator()(T x) const {
-    const T a = rn_sub(x, lo);
-    T t;
-    if (exact) {
-      t = rn_mul(a, inv);
-      t = fma(fma(-t, range, a), inv, t);
-      t = fma(fma(-t, range, a), inv, t);
-    } else {
-      t = rn_div(a, range);
-    }
-    const int j = (int)rn_mul(t, fnb);
-    return j < 0 ? 0 : (j > nb - 1 ? nb - 1 : j);
-  }
-};
-
 // one more in a thread's own counter: an LDS addition that returns nothing, so
 // the next member's does not wait for it
 __device__ __forceinline__ void count(int* c) {

@@ -20,46 +20,23 @@
 
 namespace cp {
 
-template <typename T>
-__device__ __forceinline__ T rn_sub(T a, T b);
-template <>
-__device__ __forceinline__ float rn_sub(float a, float b) {
-  return __fsub_rn(a, b);
-}
-template <>
-__device__ __forceinline__ double rn_sub(double a, double b) {
-  return __dsub_rn(a, b);
-}
-template <typename T>
-__device__ __forceinline__ T rn_add(T a, T b);
-template <>
-__device__ __forceinline__ float rn_add(float a, float b) {
-  return __fadd_rn(a, b);
-}
-template <>
-__device__ __forceinline__ double rn_add(double a, double b) {
-  return __dadd_rn(a, b);
-}
-template <typename T>
-__device__ __forceinline__ T rn_mul(T a, T b);
-template <>
-__device__ __forceinline__ float rn_mul(float a, float b) {
-  return __fmul_rn(a, b);
-}
-template <>
-__device__ __forceinline__ double rn_mul(double a, double b) {
-  return __dmul_rn(a, b);
-}
-template <typename T>
-__device__ __forceinline__ T rn_div(T a, T b);
-template <>
-__device__ __forceinline__ float rn_div(float a, float b) {
-  return __fdiv_rn(a, b);
-}
-template <>
-__device__ __forceinline__ double rn_div(double a, double b) {
-  return __ddiv_rn(a, b);
-}
+// one operation, rounded once (no contraction with its neighbours)
+#if defined(__HIP_DEVICE_COMPILE__)
+#define CP_RN(NAME, OP, F32, F64)                                                              \
+  __host__ __device__ __forceinline__ float rn_##NAME(float a, float b) { return F32(a, b); } \
+  __host__ __device__ __forceinline__ double rn_##NAME(double a, double b) { return F64(a, b); }
+#else
+#define CP_RN(NAME, OP, F32, F64)                                                            \
+  __host__ __device__ __forceinline__ float rn_##NAME(float a, float b) { return a OP b; } \
+  __host__ __device__ __forceinline__ double rn_##NAME(double a, double b) { return a OP b; }
+#endif
+CP_RN(sub, -, __fsub_rn, __dsub_rn)
+CP_RN(add, +, __fadd_rn, __dadd_rn)
+CP_RN(mul, *, __fmul_rn, __dmul_rn)
+CP_RN(div, /, __fdiv_rn, __ddiv_rn)
+#undef CP_RN
+__host__ __device__ __forceinline__ float rn_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__host__ __device__ __forceinline__ double rn_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // degenerate half-width of the range model: eps * max(1, |x|), rounded once
 template <typename T>
@@ -79,6 +56,37 @@ __device__ __forceinline__ double div_count(double a, double M, double iM) {
   q = fma(fma(-q, M, a), iM, q);
   return fma(fma(-q, M, a), iM, q);
 }
+
+// Bin of a member x of a vertex's range [lo, hi]: floor((x - lo) / (hi - lo) * nb),
+// clamped.  All members share the divisor, so the quotient is its rounded
+// reciprocal's product, corrected twice by the remainder (Markstein's scheme, as
+// div_count), five operations.  It is the division's, correctly rounded, where
+// the remainder is exact: its lowest bit is 2^-46 (FP64 2^-104) of range times
+// quotient, at least 2^-149 (2^-1074) for a range from 1e-20 (1e-200) on and a
+// quotient down to 2^-36, and a smaller one is bin 0 either way.  Ranges outside
+// the limits, infinite and NaN ones divide.
+template <typename T>
+struct BinOf {
+  T lo, range, inv, fnb;
+  int nb;
+  bool exact;
+  __host__ __device__ __forceinline__ BinOf(T lo_, T hi, int nb_) : lo(lo_), range(rn_sub(hi, lo_)), fnb(T(nb_)), nb(nb_) {
+    constexpr T kLo = sizeof(T) == 8 ? T(1e-200) : T(1e-20f), kHi = sizeof(T) == 8 ? T(1e200) : T(1e30f);
+    exact = range >= kLo && range <= kHi;
+    inv = rn_div(T(1), range);
+  }
+  // a / range
+  __host__ __device__ __forceinline__ T quotient(T a) const {
+    if (!exact) return rn_div(a, range);
+    T t = rn_mul(a, inv);
+    t = rn_fma(rn_fma(-t, range, a), inv, t);
+    return rn_fma(rn_fma(-t, range, a), inv, t);
+  }
+  __host__ __device__ __forceinline__ int operator()(T x) const {
+    const int j = (int)rn_mul(quotient(rn_sub(x, lo)), fnb);
+    return j < 0 ? 0 : (j > nb - 1 ? nb - 1 : j);
+  }
+};
 
 // Running statistics of one vertex's members, then its parameters.
 // Uniform: (lo, hi) = (min, max); Epanechnikov / Gaussian: (m, w) with

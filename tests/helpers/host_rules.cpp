@@ -6,11 +6,39 @@
 //     Philox blocks of four samples of the semianalytical estimator.
 //   host_rules thread <samples> <bins> <bytes of an element> <vertices>
 //     whether that estimator gives a vertex to a thread (1) or a wave (0).
+//   host_rules quotients <dtype> <log2 of the ranges' scale> <seed>
+//     of a million ranges in [1, 2) times the scale and members within them: how
+//     many of BinOf's quotients of 2^-36 and more differ from the division, and
+//     how many of the bins of 32 do (dtype: 0 FP32, 1 FP64).
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <random>
 
+#include "cp_fit.hpp"
 #include "cp_internal.hpp"
+
+template <typename T>
+static void quotients(int scale, unsigned seed) {
+  std::mt19937_64 rng(seed);
+  std::uniform_real_distribution<double> u(0.0, 1.0);
+  long wrong = 0, bins = 0;
+  for (int i = 0; i < 1000000; ++i) {
+    const T range = (T)std::ldexp(1.0 + u(rng), scale);
+    // quotients over 36 binades, every other one beside an edge of the 32 bins
+    T a = (T)((double)range * std::exp2(-36.0 * u(rng)));
+    if (i & 1) a = std::nextafter((T)((double)range * (double)(rng() % 33) / 32.0), u(rng) < 0.5 ? T(0) : range);
+    const cp::BinOf<T> b(T(0), range, 32);
+    const volatile T d = a / range;
+    const T q = d;
+    wrong += q >= T(1.4551915228366852e-11) && b.quotient(a) != q;
+    int j = (int)(q * T(32));
+    j = j > 31 ? 31 : j;
+    bins += b(a) != j;
+  }
+  std::printf("%ld %ld\n", wrong, bins);
+}
 
 int main(int argc, char** argv) {
   if (argc == 3 && !std::strcmp(argv[1], "blocks")) {
@@ -20,6 +48,12 @@ int main(int argc, char** argv) {
   if (argc == 6 && !std::strcmp(argv[1], "thread")) {
     std::printf("%d\n", cp::semi_by_thread(std::atoi(argv[2]), std::atoi(argv[3]), (size_t)std::atoi(argv[4]),
                                            std::atoll(argv[5])));
+    return 0;
+  }
+  if (argc == 5 && !std::strcmp(argv[1], "quotients")) {
+    const int scale = std::atoi(argv[3]);
+    const unsigned seed = (unsigned)std::atoi(argv[4]);
+    std::atoi(argv[2]) ? quotients<double>(scale, seed) : quotients<float>(scale, seed);
     return 0;
   }
   std::fprintf(stderr, "usage: see the head of this file\n");

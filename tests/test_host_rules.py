@@ -48,3 +48,12 @@ def test_semianalytical_blocks(rules, ns):
     (2**31 - 1, 32, 8, 2048, 0)])
 def test_semianalytical_form(rules, ns, nbins, el, side, thread):
     assert int(rules("thread", ns, nbins, el, side * side)[0]) == thread
+
+
+# Ranges on both sides of the limits below and above which BinOf divides, just
+# inside them and in the middle.
+@pytest.mark.parametrize("dtype,scale", [(0, s) for s in (-126, -100, -99, -98, -90, -80, -67, -66, -65, -30, 0, 60,
+                                                          98, 99, 100)] +
+                         [(1, s) for s in (-700, -665, -664, 0, 663, 664, 665)])
+def test_histogram_bin_quotients(rules, dtype, scale):
+    assert rules("quotients", dtype, scale, scale + 1000) == ["0", "0"]
