@@ -381,7 +381,7 @@ __device__ __forceinline__ void tile_hist_sweep(const FieldPtrs<T>& f, int ty0, 
 // entry and the entries of its four neighbours' stencils that refer to u
 // (own, east's w slot, west's e slot, north's s slot, south's n slot)
 template <typename T>
-__device__ __forceinline__ void hist_gather_vertex(const FieldPtrs<T>& f, const T* __restrict__ J, int64_t id) {
+CP_HD void hist_gather_vertex(const FieldPtrs<T>& f, const T* __restrict__ J, int64_t id) {
   const int64_t plane = (int64_t)f.H * f.W;
   if (id >= plane) return;
   const int y = (int)(id / f.W), x = (int)(id - (int64_t)y * f.W);
@@ -425,7 +425,7 @@ __host__ __device__ constexpr int gather_vec() {
 __host__ __device__ constexpr int64_t gather_groups(int H, int W, int V) { return (int64_t)H * ((W + V - 1) / V); }
 
 template <typename T>
-__device__ __forceinline__ void hist_gather_vec(const FieldPtrs<T>& f, const T* __restrict__ J, int64_t q) {
+CP_HD void hist_gather_vec(const FieldPtrs<T>& f, const T* __restrict__ J, int64_t q) {
   constexpr int V = gather_vec<T>();
   typedef T Vec __attribute__((ext_vector_type(V)));
   if (q >= gather_groups(f.H, f.W, V)) return;
