@@ -79,13 +79,15 @@ struct BatchField {
   int model;
 };
 
-// The FP32 histogram forward pass keeps the 5 waves per SIMD of its per-field
-// kernel (the tile loop would otherwise push it one register over), and the
-// FP32 histogram adjoint sweep 4 (at 132 registers it would drop to 3: the
-// tuned 64 x 8 variant then ran 7% longer).
-template <typename T, int PASS>
+// Waves per SIMD asked for inside the claim loop.  FP32 histogram forward: 5 (the
+// loop would otherwise push it one register over).  FP32 histogram adjoint sweep
+// in 64 x 4 tiles: 4, at the price of 28 spilled registers; in 64 x 8 tiles 3, as
+// 4 would spill 38.  Adjoint of 12 fields of 256^2 to 1260^2 x 10 bins, claimed one by one: 64 x 4
+// 2.25 ms (three waves 2.54), 64 x 8 2.48 ms (four waves 2.78).
+template <typename T, int PASS, int V>
 constexpr int batched_min_waves() {
-  return sizeof(T) == 4 && PASS == PASS_FWD_HIST ? 5 : (sizeof(T) == 4 && PASS == PASS_BWD_HIST ? 4 : 1);
+  if (sizeof(T) == 4 && PASS == PASS_FWD_HIST) return 5;
+  return sizeof(T) == 4 && PASS == PASS_BWD_HIST ? (V == 0 ? 4 : 3) : 1;
 }
 
 // Tiles are claimed in chunks of `chunk` consecutive entries (neighbouring
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(kNT) void k_batched_flat(const BatchField<T>* __res
 }
 
 template <typename T, int PASS, int V>
-__global__ __launch_bounds__(kNT, (batched_min_waves<T, PASS>())) void k_batched(
+__global__ __launch_bounds__(kNT, (batched_min_waves<T, PASS, V>())) void k_batched(
     const BatchField<T>* __restrict__ fields, const BatchTile* __restrict__ tiles, int ntiles, int chunk,
     int* queue) {
   extern __shared__ __align__(16) unsigned char smem[];
