@@ -72,6 +72,9 @@ struct MvgStencil {
   int first;      // first present neighbour, 4: none
 };
 
+//
+// Loads of absent values are skipped with DIFF and made elsewhere without it, by
+// measurement (500^2 x 64: conditional 109 us skipped and 117 made, hits 130 and 122).
 template <bool DIFF>
 __device__ __forceinline__ void load_stencil(const MvgArgs& a, int v, int lane, MvgStencil& s) {
   const int y = v / a.W, x = v - y * a.W;
@@ -83,7 +86,12 @@ __device__ __forceinline__ void load_stencil(const MvgArgs& a, int v, int lane, 
   s.first = 4;
 #pragma unroll
   for (int i = 3; i >= 0; --i) {
-    s.d[i] = pres[i] ? (float)(a.par[at + off[i]] - mv) : 0.0f;
+    if constexpr (DIFF) {
+      s.d[i] = pres[i] ? (float)(a.par[at + off[i]] - mv) : 0.0f;
+    } else {
+      const double mn = a.par[at + (pres[i] ? off[i] : 0)];
+      s.d[i] = pres[i] ? (float)(mn - mv) : 0.0f;
+    }
     d0 = pres[i] ? s.d[i] : d0;
     s.first = pres[i] ? i : s.first;
   }
@@ -95,8 +103,14 @@ __device__ __forceinline__ void load_stencil(const MvgArgs& a, int v, int lane, 
   const double* L = a.par + a.ps + at;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const double l = k <= n && n < 4 ? L[(int64_t)(n * (n + 1) / 2 + k) * a.ps] : 0.0;
-    s.row[k] = DIFF ? (float)((l - L[(int64_t)(10 + k) * a.ps]) * (double)kDeviateScale) : (float)l;
+    if constexpr (DIFF) {
+      const double l = k <= n && n < 4 ? L[(int64_t)(n * (n + 1) / 2 + k) * a.ps] : 0.0;
+      s.row[k] = (float)((l - L[(int64_t)(10 + k) * a.ps]) * (double)kDeviateScale);
+    } else {
+      const bool in = k <= n && n < 4;
+      const float l = (float)L[(int64_t)(in ? n * (n + 1) / 2 + k : 0) * a.ps];
+      s.row[k] = in ? l : 0.0f;
+    }
   }
   s.L44 = (float)L[14 * a.ps];
 }
@@ -124,13 +138,17 @@ __device__ __forceinline__ float max4(const f32x4& v) {
 // ten transcendental (eight cycles each).  500^2 x 2000: 1.71 -> 1.53 ms.  With q the upper tail of |r|,
 // Phi(r) = [r >= 0] - copysign(q, r): the first part is counted by the scalar
 // unit, and q is summed with its full relative precision.
-template <int V, bool HIT>
+//
+// VEC: the generator's keys in vector registers, which costs a wave as much as some
+// 150 samples gain (500^2, conditional estimator, in vector / in scalar registers: 64 samples 148 /
+// 109 us, 128 167 / 147, 256 238 / 238, 320 279 / 286; 64 hits 158 / 122).
+template <int V, bool HIT, bool VEC>
 __global__ __launch_bounds__(256) void k_mvg_fwd(MvgArgs a) {
   const int lane = threadIdx.x & 63;
   const int v0 = __builtin_amdgcn_readfirstlane((blockIdx.x * 4 + (threadIdx.x >> 6)) * V);
   const int nv = a.H * a.W;
   if (v0 >= nv) return;
-  const PhiloxKeys keys = philox_keys(a.k0, a.k1);
+  const PhiloxKeys keys = philox_keys<VEC>(a.k0, a.k1);
   MvgStencil s[V];
   float inv[V], invm[V], L4[HIT ? V : 1][4];
   double qmin[V], qmax[V];
@@ -362,6 +380,16 @@ __global__ __launch_bounds__(256) void k_philox_raw(int64_t n, const uint32_t* c
 
 // two vertices per wave once that still leaves four waves per SIMD
 constexpr int64_t kMvgPairVertices = 8192;
+// samples from which on the generator's keys are worth vector registers
+constexpr int kMvgVectorKeys = 256;
+
+template <bool HIT, bool VEC>
+void launch_fwd(const MvgArgs& a, bool two, dim3 grid, hipStream_t st) {
+  if (two)
+    hipLaunchKernelGGL((k_mvg_fwd<2, HIT, VEC>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_mvg_fwd<1, HIT, VEC>), grid, dim3(256), 0, st, a);
+}
 
 MvgArgs make_args(const Field& f, const double* params) {
   MvgArgs a{};
@@ -385,18 +413,11 @@ hipError_t mvg_forward(const Field& f, const double* params, float* pmin, float*
   a.pmax = pmax;
   const int64_t nv = (int64_t)f.H * f.W;
   const bool two = nv >= kMvgPairVertices;
-  const dim3 grid((unsigned)((nv + (two ? 8 : 4) - 1) / (two ? 8 : 4))), block(256);
-  if (f.est == CP_MC_HIT) {
-    if (two)
-      hipLaunchKernelGGL((k_mvg_fwd<2, true>), grid, block, 0, st, a);
-    else
-      hipLaunchKernelGGL((k_mvg_fwd<1, true>), grid, block, 0, st, a);
-  } else {
-    if (two)
-      hipLaunchKernelGGL((k_mvg_fwd<2, false>), grid, block, 0, st, a);
-    else
-      hipLaunchKernelGGL((k_mvg_fwd<1, false>), grid, block, 0, st, a);
-  }
+  const dim3 grid((unsigned)((nv + (two ? 8 : 4) - 1) / (two ? 8 : 4)));
+  if (f.ns >= kMvgVectorKeys)
+    f.est == CP_MC_HIT ? launch_fwd<true, true>(a, two, grid, st) : launch_fwd<false, true>(a, two, grid, st);
+  else
+    f.est == CP_MC_HIT ? launch_fwd<true, false>(a, two, grid, st) : launch_fwd<false, false>(a, two, grid, st);
   return hipGetLastError();
 }
 
