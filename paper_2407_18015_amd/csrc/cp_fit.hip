@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kFitTX* kFitTY) void k_fit(FitArgs a) {
 // Members are read once and the parameters written once, so both go through
 // non-temporal accesses (no cache allocation on the way): 5.7 against
 // 5.0 TB/s for this access pattern at 2048^2 x 20.
-template <typename T, int MODEL, int V, int U>
+template <typename T, int MODEL, int V, int U, bool SQ>
 __global__ __launch_bounds__(256) void k_fit_vec(FitArgs a, int64_t nvec) {
   typedef T Vec __attribute__((ext_vector_type(V)));
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_fit_vec(FitArgs a, int64_t nvec) {
   const int64_t at = (int64_t)y * a.rs + x;
   const T* mem = static_cast<const T*>(a.members);
   T* par = static_cast<T*>(a.params);
-  FitAcc<T, MODEL> acc[V];
+  FitAcc<T, MODEL, SQ> acc[V];
   {
     const Vec v = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(mem + at));
 #pragma unroll
@@ -293,12 +293,19 @@ __global__ __launch_bounds__(256) void k_fit_mvg(FitArgs a, double jitter) {
 //     800^2 9.8 / 9.5 / 10.1, 1000^2 12.6 / 13.1 / 13.9.
 // At 1024^2, members from memory, eights are slower (16.6 against 18.2), as FP64
 // is at every size.
-constexpr int64_t kFitSmall = 98304, kFitMid = 163840;
+// Between there and 295 thousand groups (1086^2) Epanechnikov and Gaussian fits by
+// fours are faster with a comparison per member than with the test of the squares
+// (FitAcc; the members then come from the last-level cache, whose reads crowd
+// without the work between them).  By comparisons / by squares, members in that
+// cache, in parentheses from memory: 820^2 10.4 / 14.0 (12.6 / 16.0), 900^2 12.7 /
+// 15.7 (15.5 / 17.0), 1024^2 15.0 / 16.6 (18.1 / 18.1), 1100^2 18.0 / 18.5
+// (20.3 / 19.9), 1200^2 21.0 / 19.6 (23.9 / 21.9), 1400^2 27.8 / 26.8 (30.7 / 29.1).
+constexpr int64_t kFitSmall = 98304, kFitMid = 163840, kFitLarge = 294912;
 
-template <typename T, int MODEL, int V, int U>
+template <typename T, int MODEL, int V, int U, bool SQ = sizeof(T) == 4>
 hipError_t launch_fit_vec(const FitArgs& a, hipStream_t st) {
   const int64_t nvec = (int64_t)a.H * (a.W / V);
-  hipLaunchKernelGGL((k_fit_vec<T, MODEL, V, U>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st, a, nvec);
+  hipLaunchKernelGGL((k_fit_vec<T, MODEL, V, U, SQ>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st, a, nvec);
   return hipGetLastError();
 }
 
@@ -312,6 +319,7 @@ hipError_t launch_fit(const FitArgs& a, hipStream_t st) {
       if constexpr (sizeof(T) == 4) {
         if (n <= kFitSmall) return launch_fit_vec<T, MODEL, 2, 8>(a, st);
         if (n <= kFitMid) return launch_fit_vec<T, MODEL, 4, 8>(a, st);
+        if (n <= kFitLarge && MODEL != CP_UNIFORM) return launch_fit_vec<T, MODEL, 4, 0, false>(a, st);
       }
       return launch_fit_vec<T, MODEL, V, 0>(a, st);
     }

@@ -100,14 +100,13 @@ struct BinOf {
 // field's type is never 0 in FP64).  A NaN member gives a NaN d, which the
 // test ignores, as the min / max comparisons ignore it; a NaN first member
 // makes every d NaN: degenerate, as !(min < max) is then.  In FP32 no square of
-// a d underflows, so the sum of squares tells as much without a comparison per
-// member; only where it is NaN are the members (member(k)) looked at again.
-template <typename T, int MODEL>
+// a d underflows, so the sum of squares tells as much (SQ) without a comparison
+// per member; only where it is NaN are the members (member(k)) looked at again.
+template <typename T, int MODEL, bool SQ = sizeof(T) == 4>
 struct FitAcc {
   T mn, mx;
   double shift, s1, s2;
   bool spread;
-  static constexpr bool kBySquares = sizeof(T) == 4;
   __device__ __forceinline__ void first(T x0) {
     if (MODEL == CP_UNIFORM) {
       mn = mx = x0;
@@ -123,7 +122,7 @@ struct FitAcc {
       mx = xk > mx ? xk : mx;
     } else {
       const double d = (double)xk - shift;
-      if (!kBySquares) spread = spread || fabs(d) > 0.0;
+      if (!SQ) spread = spread || fabs(d) > 0.0;
       s1 += d;
       s2 = fma(d, d, s2);
     }
@@ -142,7 +141,7 @@ struct FitAcc {
       }
       return;
     }
-    if (kBySquares) {
+    if (SQ) {
       spread = s2 > 0.0;
       if (s2 != s2)
         for (int k = 1; k < M; ++k) spread = spread || fabs((double)member(k) - shift) > 0.0;
