@@ -305,7 +305,9 @@ cp_status_t cp_prob_semianalytical(const cp_field_desc_t* desc, const void* para
  * the call then blocks until the trials are done, and fails (CP_EINVAL)
  * while the stream is being captured.  The trials write the outputs, with
  * the same values: no tile shape or launch form changes a result.  Without
- * the flag a plan uses the first shape and one tile per block.
+ * the flag a plan uses the first shape (the FP32 uniform / Epanechnikov
+ * adjoint of fewer than 960 30x30 tiles in all: the second, 14x14) and one
+ * tile per block.
  * Tuning table: if the environment variable CPCRIT_TUNE_CACHE names a file,
  * every plan the tuner times appends its choices there (one text line keyed
  * by the GPU architecture, its CU count and the field shapes), and a later
@@ -331,8 +333,7 @@ typedef enum {
  * Fix the tile shape and claim chunk of each pass of the plan that
  * cp_prob_batched uses for these descriptors and flags (building the plan if
  * no call has yet): shape[p] indexes the shapes listed under CP_BATCH_TUNE
- * for pass p (0 = the default; the FP32 uniform / Epanechnikov adjoint of few
- * tiles: 1), chunk[p] >= 1 tiles per claim of the
+ * for pass p (the default is given there), chunk[p] >= 1 tiles per claim of the
  * persistent launch or -1 for one tile per block; entries < 0 (shape) or of
  * any other value (chunk) keep the current choice, entries of passes the
  * plan lacks are ignored.  For callers that tuned offline and want the result

@@ -16,8 +16,8 @@
 // signature into a HIP graph and replayed.
 //
 // The one-tile-per-block form (`chunk` 0 in a plan) keeps the registers of
-// the per-field kernels (the histogram sweeps: 96 and 80 VGPRs against 109
-// and 94 inside the claim loop) and saves the claims.
+// the per-field kernels (FP32 histogram sweep and forward: 126 and 69 VGPRs, where
+// the claim loop takes 128 with spills and 89) and saves the claims.
 //
 // Every pass is its own kernel instantiation and launch: histogram
 // tiles and uniform / Epanechnikov tiles run in separate passes, so each
@@ -55,8 +55,8 @@ constexpr size_t kMaxLds = 160 * 1024;
 
 enum { PASS_FWD_UE = 0, PASS_FWD_HIST = 1, PASS_BWD_UE = 2, PASS_BWD_HIST = 3, PASS_GATHER = 4, NPASS = 5 };
 
-// Tile variants of each pass (the tuner picks one per pass; variant 0 is the
-// default).  Forward and histogram passes: 64 x (4 << v) vertices, one, two
+// Tile variants of each pass (the tuner picks one per pass; default_variant the
+// one without it).  Forward and histogram passes: 64 x (4 << v) vertices, one, two
 // or (uniform / Epanechnikov forward) four rows per thread.  Uniform /
 // Epanechnikov adjoint: output tiles of
 // bwd_ox x bwd_oy (FP32 30x30, 14x14, 62x30; FP64 14x14, 30x14, 30x30), i.e.
@@ -206,9 +206,10 @@ const void* kernel_of(int pass, int v) {
 }
 
 // Relative cost per vertex (forward, adjoint), measured on MI355X with the
-// per-field kernels at 2048^2 (uniform forward = 1: 40.6 us; uniform adjoint
-// 64.7 us, Epanechnikov forward 85 us and adjoint 147.5 us, 10-bin histogram
-// forward 0.545 ms and adjoint 1.41 ms); histograms scale with the number of
+// per-field kernels of an earlier build at 2048^2 (uniform forward = 1: 40.6 us;
+// uniform adjoint 64.7 us, Epanechnikov forward 85 us and adjoint 147.5 us, 10-bin
+// histogram forward 0.545 ms and adjoint 1.41 ms; now 40, 71, 78, 140 us, 0.404 and
+// 1.17 ms, in the same order within a pass); histograms scale with the number of
 // bin edges.  The costs only order the tiles of one pass (longest first), so
 // within a pass only the ratios between models matter.
 double vertex_cost(int model, int nb, bool bwd) {

@@ -111,7 +111,7 @@ static hipError_t fwd_typed(const Field& f, const void* params, void* pmin, void
   FieldPtrs<T> p = make_ptrs<T>(f, params, pmin, pmax, nullptr, nullptr, nullptr);
   if (f.model == CP_UNIFORM || f.model == CP_EPANECHNIKOV) {
     // 64 x 16 outputs per 256-thread block, four rows per thread: 9% faster
-    // than 64 x 4 with one row per thread (Epanechnikov, 2048^2: 65 us);
+    // than 64 x 4 with one row per thread (Epanechnikov, 2048^2: 78 us);
     // grids too small for eight such blocks per CU keep 64 x 4
     const int tx = cdiv(f.W, kFwdTX);
     const bool tall = (int64_t)tx * cdiv(f.H, 16) >= kTallTileBlocks;
@@ -171,11 +171,11 @@ static hipError_t launch_bwd_gauss(const FieldPtrs<T>& p, hipStream_t st) {
 //     1150^2 (1521) 47.7 / 44.8 / 43.2;
 //   uniform  200^2 3.7 / 5.4 / 9.0, 500^2 7.6 / 8.2 / 10.8, 720^2 12.4 / 11.5 /
 //     14.2, 960^2 19.0 / 18.0 / 17.7;
-//   Gaussian  200^2 19 / 32 / 62, 500^2 51 / 62 / 83, 840^2 (784) 114 / 122 / 141,
-//     1020^2 (1156) 160 / 168 / 173, 1150^2 203 / 214 / 204, 1250^2 (1764) 237 /
-//     245 / 232.
+//   Gaussian  200^2 16 / 28 / 52, 500^2 50 / 52 / 72, 840^2 (784) 106 / 104 / 127,
+//     1020^2 (1156) 146 / 144 / 154, 1150^2 186 / 184 / 182, 1250^2 (1764) 218 /
+//     211 / 209.
 // The shape changes no per-vertex operation: the same bits.  FP64 takes 14x14
-// throughout (Gaussian: its 241 registers leave no room for a second stencil).
+// throughout (Gaussian: its 242 registers leave no room for a second stencil).
 static int64_t tiles30(int H, int W) { return (int64_t)cdiv(W, 30) * cdiv(H, 30); }
 constexpr int64_t kBwdSmall = 448, kBwdMid = 960, kBwdGaussSmall = 1536;
 

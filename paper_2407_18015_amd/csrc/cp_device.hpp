@@ -356,9 +356,9 @@ CP_HD T uni_side_value(const UniSide<T>& s) {
 // SAD.  Returns whether there is a centre.
 //
 // Measured at 2048^2 (20-member fit, FP32; with the mask selections above and
-// v_med3 clamps, against one centre per side): Epanechnikov forward 77 -> 65 us,
-// adjoint 133 -> 119, uniform forward 42.6 -> 37.2, adjoint 64.6 -> 62.6; all
-// are bound by vector issue, of which the selections took a fifth.
+// v_med3 clamps, against one centre per side): Epanechnikov forward 92 -> 78 us,
+// adjoint 159 -> 140, uniform forward 45 -> 40, adjoint 71 both; all are bound by
+// vector issue, of which the selections took a fifth.
 template <typename T, bool SAD>
 CP_HD bool uni_centre(T Lv, T iLv, const T (&a)[4], const T (&b)[4], const T (&iL)[4], T (&out)[4]) {
   const T l = fmax_nn(fmax_nn(fmax_nn(T(0), a[0]), fmax_nn(a[1], a[2])), a[3]);

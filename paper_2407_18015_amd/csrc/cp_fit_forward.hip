@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void k_fit_fwd_ue(FitFwdArgs<T> a, int tiles_x
   // 38.7); FP32, with twice the waves, is slower so (5% at 2048^2)
   if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(2);
   // FP32 fetches its members in chunks with no serial remainder: 64 x 12 tiles
-  // by eights (2048^2 x 20, Epanechnikov 113 -> 106 us against fours and a
+  // by eights (2048^2 x 20, Epanechnikov: 6% faster than by fours and a
   // remainder one by one); 64 x 4 tiles in groups of two vertices, which employ
   // 204 of the 256 threads (of four: 108), by sixes (720 x 1440 x 20,
   // Epanechnikov 35.0 -> 31.7 us, uniform 26.0 -> 21.0; 500^2 the same).  FP64
@@ -142,8 +142,8 @@ template <typename T, int MODEL>
 hipError_t launch(const FitFwdArgs<T>& a, hipStream_t st) {
   // 64 x 12 tiles: the 14 staged rows of 16-byte groups (252 in FP32) take
   // the 256 threads once (FP64's 476 twice); grids with fewer than eight
-  // such tiles per CU use 64 x 4.  Measured at 2048^2 (Epanechnikov, 20 members): 64 x 12 106 us
-  // (64 x 16, two passes of groups, 5% more), fit then forward 131 us.
+  // such tiles per CU use 64 x 4.  Measured at 2048^2 (Epanechnikov, 20 members): 64 x 12 102 us
+  // (64 x 16, two passes of groups, 5% more), fit then forward 136 us.
   const int tx = (a.f.W + kFwdTX - 1) / kFwdTX;
   const bool tall = (int64_t)tx * ((a.f.H + 11) / 12) >= kTallTileBlocks;
   const int TYr = tall ? 12 : 4, n = tx * ((a.f.H + TYr - 1) / TYr);

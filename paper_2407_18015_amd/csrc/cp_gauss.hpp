@@ -41,14 +41,13 @@
 //
 // Bound by vector issue.  A tail is one reciprocal, one exponential and nine
 // fused multiply-adds in FP32; in FP64 a ratio of polynomials and the density's
-// own exponential: two nodes take 484 vector instructions (adjoint 530) against
-// 753 (983) with the library's erfc and exp.  Measured at 1024^2 on a 20-member fit, FP32,
-// composite rule for every vertex -> this: classification 544 -> 88 us,
-// adjoint 1156 -> 158 us.  Sigmas drawn over a factor of 300 (most
-// waves then hold composite vertices): 165 -> 136 and 564 -> 424 us at 512^2.
-// FP64 at 1024^2, sigmas within 20%, erfc and exp -> this: 638 -> 415 and
-// 1121 -> 617 us (the composite rule took 2.16 and 3.85 ms at 512^2); 512^2 over a factor of 300
-// 1646 -> 1097 and 3121 -> 1756 us.
+// own exponential: two nodes take about 500 vector instructions (adjoint 550)
+// against 753 (983) with the library's erfc and exp.  Measured on a 20-member fit
+// of 1024^2, composite rule for every vertex (FP64: with erfc and exp) -> this:
+// FP32 classification 543 -> 106 us, adjoint 1145 -> 159 us; FP64 8.4 -> 0.51 and
+// 13.6 -> 0.74 ms.  Sigmas drawn over a factor of 300 (most waves then hold
+// composite vertices), 512^2: FP32 181 -> 177 and 561 -> 278 us, FP64 2.13 -> 1.13
+// and 3.81 -> 1.79 ms.
 #pragma once
 
 #include <cmath>

@@ -206,9 +206,9 @@ CP_HD void vertex_bins_step(VertexBins<T>& b, int E, T hv) {
 // the two mixed products are two more exact integrals (the caller keeps them
 // only for vertices with all four neighbours).
 //
-// Bound by vector issue: about 295 cycles per wave and interval, half of them
+// Bound by vector issue: about 300 cycles per wave and interval, half of them
 // the five cursor branches (a wave's lanes cross different edges, so all of
-// them run).  P_min / P_max at 2048^2 x 10 bins: 0.508 -> 0.44 ms, of which the
+// them run).  P_min / P_max at 2048^2 x 10 bins: 0.506 -> 0.404 ms, of which the
 // staging found every cell once instead of per plane gave 0.04.
 template <typename T, bool SAD = false>
 __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const int (&en)[4], const bool (&pres)[4],
@@ -255,7 +255,7 @@ __host__ __device__ void hist_vertex_sweep(const HistSuf<T>& L, int ev, const in
     // vertex's density with its whole bin: with a rounded midpoint and one sum
     // over all intervals the probabilities rounded worse than the end values'
     // (rms, FP32 and 4 bins 1.13 times, FP64 and 10 bins 1.1; so 1.04 and 0.9;
-    // it costs 1% of the sweep).
+    // it costs the forward 2%).
     const T hl = (x1 - x0) * T(0.5);
     T S[4], F[4], t[4];
 #pragma unroll

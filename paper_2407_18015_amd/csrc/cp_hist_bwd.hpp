@@ -45,10 +45,10 @@ namespace cp {
 // branch with the state updated in place: selects cost four issue cycles each,
 // and each interval ran the four of every cursor although it ends one or two
 // bins.  Bound by vector issue, 535 cycles per wave and interval (760 before;
-// both nodes unrolled, places as running pointers: 118 registers, four waves
+// both nodes unrolled, places as running pointers: 126 registers, four waves
 // per SIMD, where rolled nodes and five waves took 2% longer), and beyond the
-// caches by the entries' stores (JRow).  Adjoint at 2048^2 x 10 bins 1.41 ->
-// 1.14 ms, at 1024^2 on a rough ensemble 0.51 -> 0.30.
+// caches by the entries' stores (JRow).  Adjoint with ten bins, 2048^2 1.29 ->
+// 1.17 ms, 1024^2 0.335 -> 0.298.
 //
 // J.at(slot, k) is the place of an entry, J.step moves it to the next bin's,
 // J.put emits there and J.tail(i, value) the tail of neighbour i; slot 0 is the

@@ -21,8 +21,8 @@
 // Epanechnikov model 4, 6, 4, 6, 4 nodes beside the centre instead of 5 x 7.
 //
 // Measured (all four outputs of a 20-member fit, against five pieces with four
-// clamped factors each): 2048^2 in FP32 Epanechnikov 257 -> 129 us, uniform
-// 109 -> 56; 1024^2 in FP64 141 -> 66 and 62 -> 32.
+// clamped factors each): 2048^2 in FP32 Epanechnikov 273 -> 137 us, uniform
+// 117 -> 60; 1024^2 in FP64 165 -> 77 and 70 -> 35.
 #pragma once
 
 #include "cp_device.hpp"
